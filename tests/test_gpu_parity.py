@@ -67,9 +67,7 @@ def check_assignment(S: np.ndarray, res, eps: float, opt=None, unique_gap=None, 
 
 @pytest.mark.parametrize("d", [264, 256])
 def test_affinity_bf16_integer_inputs_bit_exact(d):
-    # T and E ragged against both tilings (64 x 128 and 128 x 128 tokens x
-    # experts); d = 264 takes the register-staged kernel, d = 256 (a multiple
-    # of 64) the pipelined one
+    # T, E and (d = 264) the contraction ragged against the tiles
     H, W = wl.small_integer_inputs(300, 200, d, seed=7)
     S = gpu_affinity(wl.f32_to_bf16_bits(H), wl.f32_to_bf16_bits(W))
     np.testing.assert_array_equal(S.astype(np.float64), oracle.affinity(H, W))
@@ -113,6 +111,34 @@ def test_affinity_workloads(name):
     err = np.abs(S - oracle.affinity(inp.H, inp.W))
     assert np.all(err <= affinity_bound(inp.H, inp.W, AFF_TOL[inp.wl.dtype]))
     assert np.all(err <= fp32_accumulation_bound(inp.H, inp.W))
+
+
+# Shapes for which the tile rule takes each of its tiles (bf16: 256 x 256, 256 x
+# 128, 256 x 64, 128 x 128, 128 x 64, 64 x 64, 32 x 32; fp32: 256 x 128, 256 x
+# 64, 128 x 64, 64 x 64, 32 x 32), one past a whole number of tiles in T, not
+# a multiple in E; d below, at and past a chunk, and with a part chunk.
+@pytest.mark.parametrize("dtype,T,E,d", [
+    ("bf16", 32769, 200, 72), ("bf16", 16385, 200, 128), ("bf16", 32769, 50, 136),
+    ("bf16", 16385, 100, 264), ("bf16", 16385, 60, 56), ("bf16", 8193, 60, 520),
+    ("bf16", 1025, 60, 1000), ("f32", 65025, 120, 40), ("f32", 65025, 50, 32),
+    ("f32", 16385, 60, 72), ("f32", 8193, 120, 24), ("f32", 1025, 60, 1000)])
+def test_affinity_every_tile(dtype, T, E, d):
+    rng = np.random.Generator(np.random.PCG64(T + 7 * E + d))
+    H = rng.standard_normal((T, d), dtype=np.float32)
+    W = rng.standard_normal((E, d), dtype=np.float32) / np.float32(np.sqrt(d))
+    Hs, Ws = H, W
+    if dtype == "bf16":
+        Hs, Ws = wl.f32_to_bf16_bits(H), wl.f32_to_bf16_bits(W)
+        H, W = wl.bf16_bits_to_f32(Hs), wl.bf16_bits_to_f32(Ws)
+    S = gpu_affinity(Hs, Ws)
+    assert np.all(np.abs(S - oracle.affinity(H, W)) <= fp32_accumulation_bound(H, W))
+    # through an index: the same bits for the same rows, zero rows out of range
+    rows = rng.integers(-1, T + 1, T).astype(np.int32)
+    Sg = host(pb.affinity(dev(Hs), dev(Ws), rows=dev(rows)))
+    ok = (rows >= 0) & (rows < T)
+    assert not Sg[~ok].any()
+    Hg = Hs[np.where(ok, rows, 0)]
+    np.testing.assert_array_equal(Sg[ok], gpu_affinity(Hg, Ws)[ok])
 
 
 # ---------------------------------------------------------------- assign ---
