@@ -53,6 +53,8 @@ constexpr int kRangeBlocks = 256;   // blocks of the score-range reduction
 constexpr int kPrologueBlocks = 4096;   // largest grid of the prologue (one range partial each)
 constexpr int kCountTile = 256;  // tokens per block in the permutation build
 constexpr int kWideLoopRounds = 1024;  // rounds one launch of the round loop may run
+constexpr int kLoopMaxBlocks = 128;    // its blocks per problem (two flag words per polling lane)
+constexpr int kLoopFlags = 2 * kLoopMaxBlocks;
 constexpr int kCheckBlocks = 4096;     // largest grid of the phase check
 // Experts the shortest-path finish serves: its exchange matrix then takes 16
 // registers per thread (64 at E = 256 would leave too few for the rest of
@@ -117,7 +119,7 @@ inline void debug_note(const char *what, hipError_t err) {
 
 struct Layout {
     size_t ctrl, prices, hcount, hsel, bcount, holders, bucket, ovf_key, ovf_exp, active, blk,
-        eck, ecs, ecn, sums, bar, rpart, gpart, sspm, sspa, sspt, total;
+        eck, ecs, ecn, sums, rpart, gpart, sspm, sspa, sspt, total;
     int64_t cap, nblk;
 };
 
@@ -143,8 +145,9 @@ Layout make_layout(int64_t T, int64_t E) {
     L.ecs = off;     off += align_up((size_t)E * 64 * 2);
     L.ecn = off;     off += align_up((size_t)E * 4);
     L.sums = off;    off += align_up((size_t)T * 64);          // per-token score summaries
-    L.bar = off;     off += align_up(512);                      // grid barrier words
-    L.rpart = off;   off += align_up((size_t)kPrologueBlocks * 12);   // score-range partials
+    // Score-range partials; once the start kernel has read them, the round
+    // loop's barrier words.
+    L.rpart = off;   off += align_up((size_t)kPrologueBlocks * 12);
     L.gpart = off;   off += align_up((size_t)kCheckBlocks * 8);    // phase-check partials
     // The exchange matrix of the shortest-path finish (E <= 256 only):
     // cheapest move from expert e to expert x and the slot of its token.
@@ -176,7 +179,7 @@ struct Ctx {
     uint16_t *eng_cs;
     int *eng_cn;
     uint32_t *sums;   // T x 16 words: each token's 8 best scores, their experts, a bound
-    uint64_t *bar;    // grid barrier: arrivals at bar[0], release at bar[32] (own lines)
+    uint64_t *flags;  // the round loop's barrier words [2][kLoopMaxBlocks]
     double *gpart;    // per-block partial sums of the phase check
     int ssp_cap;      // > 0: a phase with at most this many active tokens left is finished
                       // by shortest augmenting paths
@@ -215,7 +218,7 @@ struct Ctx {
         r.eng_cs = shift(eng_cs, w);
         r.eng_cn = shift(eng_cn, w);
         r.sums = shift(sums, w);
-        r.bar = shift(bar, w);
+        r.flags = shift(flags, w);
         r.gpart = shift(gpart, w);
         r.ssp_m = shift(ssp_m, w);
         r.ssp_a = shift(ssp_a, w);
@@ -251,7 +254,7 @@ Ctx<M> make_ctx(const void *S, const AssignParams &p, char *ws) {
     c.eng_cs = reinterpret_cast<uint16_t *>(ws + L.ecs);
     c.eng_cn = reinterpret_cast<int *>(ws + L.ecn);
     c.sums = reinterpret_cast<uint32_t *>(ws + L.sums);
-    c.bar = reinterpret_cast<uint64_t *>(ws + L.bar);
+    c.flags = reinterpret_cast<uint64_t *>(ws + L.rpart);
     c.gpart = reinterpret_cast<double *>(ws + L.gpart);
     c.ssp_cap = 0;
     c.ssp_m = reinterpret_cast<float *>(ws + L.sspm);
@@ -739,6 +742,34 @@ __device__ inline void load_summary(const uint32_t *sums, int t, int gl, uint32_
 // the best over all experts (with the same lowest-index tie rule, as no
 // outside expert can tie it), and a second value reaching the limit is the
 // second best over all experts.
+//
+// top2_entries: the top-2 over the entries (lanes gl < 8 of a group of eight),
+// and whether it is the top-2 over all experts.
+template <class M>
+__device__ inline bool top2_entries(const Ctx<M> &c, const uint32_t (&sw)[4], bool valid, int gl,
+                                    const typename M::value_t *pr, typename M::value_t pmin,
+                                    typename M::value_t &v1, int &e1, typename M::value_t &v2,
+                                    typename M::value_t &s1) {
+    using value_t = typename M::value_t;
+    const int cnt = (int)sw[3];
+    v1 = M::lowest();
+    v2 = M::lowest();
+    s1 = 0;
+    e1 = 0x7fffffff;
+    if (valid && gl < cnt) {
+        const value_t sc = bits_score<M>(sw[0], c.scale);
+        int ex = (int)((sw[1] >> (16 * (gl & 1))) & 0xffff);
+        if (ex >= c.E) ex = 0;
+        v1 = sc - pr[ex];
+        e1 = ex;
+        s1 = sc;
+    }
+    top2_reduce<M, 8>(v1, e1, v2, s1);
+    if (cnt >= c.E) return true;
+    const value_t lim = bits_score<M>(sw[2], c.scale) - pmin;
+    return v1 > lim && v2 >= lim;
+}
+
 template <class M, int G>
 __device__ inline void top2_summary(const Ctx<M> &c, const uint32_t (&sw)[4], int t, bool valid,
                                     int gl, const typename M::value_t *pr,
@@ -994,7 +1025,8 @@ __device__ inline void for_each_candidate(const Ctx<M> &c, int e, const uint64_t
 
 // Suffix scan of sm.hist by wave 0: finds the digit holding the need-th
 // largest candidate; stores it in sm.sel_digit and the remaining rank in sm.need.
-__device__ inline void pick_digit(UpdateSmem &sm, int need) {
+template <class SM>
+__device__ inline void pick_digit(SM &sm, int need) {
     if (threadIdx.x < 64) {
         const int l = threadIdx.x;
         // Lane l owns digits 255-4l .. 252-4l (descending).
@@ -1575,9 +1607,9 @@ __global__ void phase_begin_kernel(Ctx<M> c0, AssignParams p, int nparts) {
         const bool finished = ctrl->phase > 0 && !ctrl->all_active &&
                               ld_relaxed(&ctrl->active_count[ctrl->cur]) == 0;
         check = nparts > 0 && !ctrl->done && !ctrl->last_phase && finished && !ctrl->skip_check;
-        c.bar[0] = 0;    // the round loop's barrier counts from zero in every launch
-        c.bar[32] = 0;
     }
+    // The round loop's barriers count from one in every launch.
+    for (int i = threadIdx.x; i < kLoopFlags; i += blockDim.x) c.flags[i] = 0;
     __syncthreads();
     if (check) phase_check_decide<M>(c, nparts);
     __syncthreads();
@@ -1653,11 +1685,11 @@ __global__ __launch_bounds__(256) void start_kernel(Ctx<M> c0, AssignParams p, c
             const double floor_eps = ldexp(mag, -20);
             if (ctrl->eps_final_eff < floor_eps) ctrl->eps_final_eff = floor_eps;
         }
-        c.bar[0] = 0;    // the round loop's barrier counts from zero in every launch
-        c.bar[32] = 0;
         begin_phase_scalar(ctrl, p, c.T);
         begin_phase_early(ctrl);
     }
+    // The partials have been read: the round loop's barrier words take their place.
+    for (int i = threadIdx.x; i < kLoopFlags; i += blockDim.x) c.flags[i] = 0;
     for (int e = threadIdx.x; e < c.E; e += blockDim.x) {
         c.hcount[e] = 0;
         c.hsel[e] = 0;
@@ -1723,144 +1755,1069 @@ __global__ __launch_bounds__(kThreads) void update_wide_kernel(Ctx<M> c0) {
     }
 }
 
-// ------------------------------------------------------ wide round loop --
+// ----------------------------------------------------------- round loop --
 //
-// Rounds that still have more active tokens than the engine takes after
-// the fixed wide launches: one block per compute unit runs them back to
-// back with a grid barrier between the bids and the updates and after the
-// updates (the last block to finish closes the round). The launch follows
-// the stream's previous kernels, so on the idle device every block is
-// resident at once (each compute unit holds at least one; the host checks
-// the occupancy). A cooperative launch would guarantee that too, but costs
-// 20-40 us per launch here against about 2.5 us for a plain one, and this
-// kernel is launched once per phase slot. The barrier's wait is bounded,
-// so a block that never got scheduled ends the loop with an internal
-// error, not a hang. All blocks read the same control words after a barrier and take
-// the same exit. The launch returns at once when there is nothing to do.
+// The rounds of a phase that have more active tokens than the engine takes:
+// a few blocks per problem (128 for a single one, half the compute units) run
+// them back to back in one launch, two grid barriers a round. Bound by latency, so the round
+// is laid out for few dependent trips to memory and no atomic on it:
+//   - Block b owns positions [b per, (b + 1) per) of the phase's bid table
+//     and the experts [b pe, (b + 1) pe). Its active tokens sit at the front
+//     of its positions, so their number is the only count others need.
+//   - A bid goes to its token's own position (key, expert): nothing is
+//     reserved, nothing collides on a popular expert.
+//   - After a barrier the owner of an expert scans the experts of all bids
+//     (two bytes each, only the filled front of every block's positions) and
+//     collects its own. It keeps the C largest keys of holders and bids; the
+//     token each bid leaves active (the bidder refused, the holder it
+//     displaced, none for a free slot) goes to the bid's position of an out
+//     table.
+//   - After a second barrier every block reads its own positions of the out
+//     table back and packs them.
+// The barrier is an array of flags, one word per block: a block stores its
+// word (the barrier's number, and a count for the others: its bids, or the
+// tokens its experts left active), and one wave reads all words until every
+// one has arrived. Everything that crosses blocks goes by agent-scope stores
+// and loads, so no barrier writes back or invalidates a cache.
+//
+// A round of a few hundred active tokens takes about 10 us: ten dependent trips to memory (prices,
+// summaries, bids, flags, ...) of some 0.8 us, and the selections. With a
+// counter barrier, device-scope fences and bucket slots reserved by atomics
+// (about 70 ns each on one address) it took 26. Solves: T = 65536, E = 256
+// 3480 -> 2955 us, T = 32768, E = 128 (clustered) 991 -> 903, T = 2048, E = 128
+// 758 -> 743. Finding an expert's threshold costs most of a large round: bit
+// by bit over the block (two bits a barrier) took 10-20 us, the histograms
+// 4-6; reading the list from registers instead of LDS spilled.
+//
+// Every block of the grid must be resident at once. The launch follows the
+// stream's previous kernels, so on the idle device it is (the host checks
+// the occupancy: two blocks to a compute unit, so that four solves on
+// streams of their own fit together). The waits are bounded: a block never scheduled ends the solve
+// with an internal error, not a hang. (A cooperative launch would guarantee
+// residency, but costs 20-40 us here against 2.5 us for a plain one.) The
+// launch returns at once when there is nothing to do.
+constexpr int kLoopThreads = 512;
+constexpr int kLoopWaves = kLoopThreads / 64;
+constexpr int kLoopCand = 5120;      // bids of a block's experts staged in LDS (12 bytes each)
+constexpr int kLoopCandMin = 4096;
+constexpr int kLoopOwned = 255;      // experts per block (the high byte of a staged position)
+constexpr int kLoopWaveBids = 192;   // bids of an expert one wave takes (the block above that)
+constexpr int kLoopToks = 1024;      // positions of a block whose tokens stay in LDS
+constexpr size_t kLoopLdsMax = 79 * 1024;   // two blocks per compute unit
 
-// Barrier k of a launch completes when bar[0] reaches k * gridDim.x. Every
-// thread waits for its own stores first; one thread per block then writes
-// back its L2 (device-scope release), arrives, waits for the release word
-// (on its own line, stored by the last arrival) and invalidates its caches
-// (acquire). The wait gives up after `poll_limit` polls (2^24 by default,
-// about a second): the block flags an internal error and returns false.
-__device__ inline bool grid_barrier(uint64_t *bar, uint64_t target, SolveCtrl *ctrl,
-                                    uint32_t poll_limit) {
+struct LoopLds {
+    size_t pr, hc, hs, lec, cnt, toks, und, scr, key, pos, total;
+    int cap;
+};
+__host__ __device__ inline LoopLds loop_lds(int E, int vbytes, int nb) {
+    LoopLds L{};
+    const int pe = (E + nb - 1) / nb;
+    size_t off = 0;
+    L.pr = off;   off = (off + (size_t)E * vbytes + 15) & ~size_t(15);
+    L.hc = off;   off = (off + (size_t)pe * 4 + 15) & ~size_t(15);
+    L.hs = off;   off = (off + (size_t)pe * 4 + 15) & ~size_t(15);
+    L.lec = off;  off = (off + (size_t)pe * 4 + 15) & ~size_t(15);
+    L.cnt = off;  off += (size_t)kLoopMaxBlocks * 4;
+    L.toks = off; off += (size_t)kLoopToks * 4;
+    L.und = off;  off += (size_t)kLoopToks * 2;
+    L.scr = off;  off += (size_t)kLoopWaves * 2 * 64 * 8;   // wave scratch, or the histogram
+    int cap = (int)((kLoopLdsMax - off) / 12) & ~63;
+    cap = cap > kLoopCand ? kLoopCand : (cap < kLoopCandMin ? kLoopCandMin : cap);
+    L.cap = cap;
+    L.key = off;  off += (size_t)cap * 8;
+    L.pos = off;  off += (size_t)cap * 4;
+    L.total = off;
+    return L;
+}
+
+// Agent-scope accesses of the data that crosses blocks inside the loop.
+template <class T>
+__device__ inline T ld_agent(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ inline void st_agent(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline float ld_price(const float *p) {
+    return __uint_as_float(ld_agent(reinterpret_cast<const uint32_t *>(p)));
+}
+__device__ inline int64_t ld_price(const int64_t *p) { return ld_agent(p); }
+__device__ inline void st_price(float *p, float v) {
+    st_agent(reinterpret_cast<uint32_t *>(p), __float_as_uint(v));
+}
+__device__ inline void st_price(int64_t *p, int64_t v) { st_agent(p, v); }
+
+// Barrier number `seq` (1, 2, ... within a launch) of the loop's nb blocks
+// over the flag words [2][kLoopMaxBlocks], odd and even barriers in halves of
+// their own: a block reaches barrier seq + 2 only after every block has read
+// the words of seq. `payload` (31 bits, thread 0's) reaches every block:
+// cnt[k] is block k's. Returns false when the wait gave up.
+constexpr uint32_t kLoopErr = 0x80000000u;   // payload bit: the block saw an error
+__device__ inline bool loop_barrier(uint64_t *flags, uint32_t seq, int nb, uint32_t payload,
+                                    int *cnt, SolveCtrl *ctrl, uint32_t poll_limit) {
     __shared__ int ok;
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores are done
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores have arrived
     __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const uint64_t arrived =
-            __hip_atomic_fetch_add(bar, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
-        if (arrived == target) {
-            __hip_atomic_store(bar + 32, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            uint32_t polls = 0;
-            while (__hip_atomic_load(bar + 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-                if (polls >= poll_limit) {
-                    flag_internal(ctrl);
-                    ok = 0;
-                    break;
-                }
-                ++polls;
-                __builtin_amdgcn_s_sleep(2);
+    uint64_t *w = flags + (seq & 1) * kLoopMaxBlocks;
+    if (threadIdx.x == 0) st_agent(w + blockIdx.x, ((uint64_t)seq << 32) | payload);
+    if (threadIdx.x < 64) {
+        const int l = threadIdx.x;
+        uint64_t a = 0, b = 0;
+        int fine = 1;
+        for (uint32_t polls = 0;; ++polls) {
+            a = l < nb ? ld_agent(w + l) : (uint64_t)seq << 32;
+            b = l + 64 < nb ? ld_agent(w + l + 64) : (uint64_t)seq << 32;
+            if (__ballot((uint32_t)(a >> 32) != seq || (uint32_t)(b >> 32) != seq) == 0) break;
+            if (polls >= poll_limit) {
+                fine = 0;
+                break;
             }
+            __builtin_amdgcn_s_sleep(1);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        cnt[l] = (int)(uint32_t)a;
+        cnt[l + 64] = (int)(uint32_t)b;
+        if (l == 0) {
+            ok = fine;
+            if (!fine) flag_internal(ctrl);
+        }
     }
     __syncthreads();
     return ok != 0;
 }
 
-// As grid_barrier, and the block that arrives last runs on_last() (thread 0,
-// after an acquire: every block's writes before its arrival are visible)
-// before it releases the others, which then see its writes. This folds a
-// round's closing step into the barrier that ends the round instead of a
-// separate last-block counter (one fewer chain of device atomics on one
-// address per round).
-template <class F>
-__device__ inline bool grid_barrier_last(uint64_t *bar, uint64_t target, SolveCtrl *ctrl,
-                                         uint32_t poll_limit, F on_last) {
-    __shared__ int ok;
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores are done
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ok = 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const uint64_t arrived =
-            __hip_atomic_fetch_add(bar, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
-        if (arrived == target) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            on_last();
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __hip_atomic_store(bar + 32, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            uint32_t polls = 0;
-            while (__hip_atomic_load(bar + 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-                if (polls >= poll_limit) {
-                    flag_internal(ctrl);
-                    ok = 0;
-                    break;
-                }
-                ++polls;
-                __builtin_amdgcn_s_sleep(2);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+__device__ inline uint32_t wave_min_u32(uint32_t v) {
+    uint32_t o;
+    o = grp_partner<1>(v); v = o < v ? o : v;
+    o = grp_partner<2>(v); v = o < v ? o : v;
+    o = grp_partner<4>(v); v = o < v ? o : v;
+    o = grp_partner<8>(v); v = o < v ? o : v;
+    uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
+#pragma unroll
+    for (int q = 1; q < 4; ++q) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)v, 16 * q);
+        r = x < r ? x : r;
     }
-    __syncthreads();
-    return ok != 0;
+    return r;
+}
+__device__ inline uint64_t wave_min_u64(uint64_t v) {
+    uint64_t o;
+    o = grp_partner<1>(v); v = o < v ? o : v;
+    o = grp_partner<2>(v); v = o < v ? o : v;
+    o = grp_partner<4>(v); v = o < v ? o : v;
+    o = grp_partner<8>(v); v = o < v ? o : v;
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    uint64_t r = ~0ull;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint64_t x = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, 16 * q) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)lo, 16 * q);
+        r = x < r ? x : r;
+    }
+    return r;
 }
 
-template <class M, int G>
-__global__ __launch_bounds__(kThreads) void wide_loop_kernel(Ctx<M> c0, int max_wide,
-                                                             int32_t max_rounds,
-                                                             uint32_t poll_limit) {
+// Orders one wave's LDS accesses for the compiler (the hardware keeps a
+// wave's accesses in order).
+__device__ inline void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Where to look next for the threshold that C keys reach: between lo, which
+// clo > C keys reach, and hi > lo + 1, which chi < C reach (compared in the
+// keys' upper words), by the share of the counts; the middle every third time.
+__device__ inline uint32_t next_trial(uint32_t lo, uint32_t hi, int clo, int chi, int C, int it) {
+    const uint32_t w = hi - lo;
+    const float f = it % 3 == 2 ? 0.5f : (float)(clo - C) / (float)(clo - chi);
+    uint32_t t = lo + (uint32_t)(f * (float)w);
+    t = t <= lo ? lo + 1 : t;
+    return t >= hi ? hi - 1 : t;
+}
+
+// The threshold of a selection over the wave's keys (kk and b; 0 = none,
+// more than C in all): a value that exactly C of them reach. Searched in the
+// keys' upper words by interpolation (five or six counts for a few hundred
+// keys; bit by bit from the top it was over twenty); keys that agree in them
+// are told apart by the lower words, bit by bit.
+constexpr int kLoopFew = 12;
+template <int NQ>
+__device__ inline uint64_t wave_threshold(const uint64_t (&kk)[NQ], uint64_t b, int C) {
+    uint32_t mn = b != 0 ? (uint32_t)(b >> 32) : ~0u, mx = (uint32_t)(b >> 32);
+    int n = __popcll(__ballot(b != 0));
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const uint32_t h = (uint32_t)(kk[q] >> 32);
+        mn = kk[q] != 0 && h < mn ? h : mn;
+        mx = h > mx ? h : mx;
+        n += __popcll(__ballot(kk[q] != 0));
+    }
+    uint32_t lo = wave_min_u32(mn);
+    if (n - C <= kLoopFew) {
+        // Few keys to leave: the next larger upper word, n - C times.
+        int reach = n;
+        for (uint32_t t = lo;;) {
+            int k = __popcll(__ballot((uint32_t)(b >> 32) == t && b != 0));
+            uint32_t nx = (uint32_t)(b >> 32) > t ? (uint32_t)(b >> 32) : ~0u;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const uint32_t x = (uint32_t)(kk[q] >> 32);
+                k += __popcll(__ballot(x == t && kk[q] != 0));
+                nx = x > t && x < nx ? x : nx;
+            }
+            if (reach - k < C) break;   // (keys that agree: told apart below)
+            reach -= k;
+            t = wave_min_u32(nx);
+            lo = t;
+            if (reach == C) return (uint64_t)t << 32;
+        }
+    }
+    uint32_t hi = ~wave_min_u32(~mx);
+    int clo = n, chi = 0;
+    hi = hi == ~0u ? hi : hi + 1;   // (~0: an overflowed bid, told apart below)
+    for (int it = 0; hi - lo > 1; ++it) {
+        const uint32_t t = next_trial(lo, hi, clo, chi, C, it);
+        int k = __popcll(__ballot((uint32_t)(b >> 32) >= t));
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) k += __popcll(__ballot((uint32_t)(kk[q] >> 32) >= t));
+        if (k == C) return (uint64_t)t << 32;
+        if (k > C) {
+            lo = t;
+            clo = k;
+        } else {
+            hi = t;
+            chi = k;
+        }
+    }
+    uint64_t thr = (uint64_t)lo << 32;
+    const bool open = hi == ~0u;   // (the upper words may also be ~0)
+    for (int bit = open ? 32 : 31; bit >= 0; --bit) {
+        const uint64_t trial = thr + (1ull << bit);
+        if (trial < thr) continue;
+        int k = __popcll(__ballot(b >= trial));
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) k += __popcll(__ballot(kk[q] >= trial));
+        if (k >= C) thr = trial;
+        if (k == C) break;
+    }
+    return thr;
+}
+
+// One wave merges an expert's bids, entries of the staged list with this
+// local expert, into its holders kk (h of them, written through to hold).
+// Returns the number of holders after.
+// (slot 64 q + lane of the holders in kk[q], 0: none)
+template <class M, int NQ>
+__device__ inline int loop_update_wave(const Ctx<M> &c, uint64_t (&kk)[NQ], int h,
+                                       uint64_t *hold, uint32_t le, const uint64_t *key,
+                                       const uint32_t *pos, int m, int *out, uint64_t *acc,
+                                       uint64_t *ev) {
+    const int lane = lane_id();
+    const int C = c.C;
+    for (int i0 = 0; i0 < m; i0 += 64) {
+        const int i = i0 + lane;
+        const uint32_t at = i < m ? pos[i] : ~0u;
+        const bool mine = i < m && (at >> 24) == le;
+        const uint64_t bm = __ballot(mine);
+        if (bm == 0) continue;
+        const uint64_t b = mine ? key[i] : 0ull;
+        const int k = __popcll(bm);
+        const int room = C - h;
+        uint64_t thr = 0;   // keys from here up stay
+        if (k > room) thr = wave_threshold<NQ>(kk, b, C);
+        const bool keep = mine && b >= thr;
+        const uint64_t km = __ballot(keep);
+        const int rank = __popcll(km & lanemask_lt());
+        if (keep) acc[rank] = b;
+        int ne = 0;
+        int er[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            er[q] = -1;
+            const bool leave = kk[q] != 0 && kk[q] < thr;
+            const uint64_t lm = __ballot(leave);
+            if (leave) {
+                er[q] = ne + __popcll(lm & lanemask_lt());
+                if (er[q] < 64) ev[er[q]] = kk[q];
+                else flag_internal(c.ctrl);
+            }
+            ne += __popcll(lm);
+        }
+        wave_order();
+        const int nk = __popcll(km);
+        int o = -1;
+        if (mine) {
+            if (!keep) o = key_token(b);
+            else if (rank >= room) o = rank - room < ne ? key_token(ev[(rank - room) & 63]) : -1;
+            st_agent(&out[at & 0xffffffu], o);
+        }
+        const int h1 = h + nk < C ? h + nk : C;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int s = 64 * q + lane;
+            int from = -1;
+            if (er[q] >= 0) from = room + er[q];
+            else if (s >= h && s < h1) from = s - h;
+            if (from >= 0 && from < 64 && s < C) {
+                kk[q] = acc[from];
+                hold[s] = kk[q];
+            }
+        }
+        h = h1;
+        wave_order();
+    }
+    return h;
+}
+
+// LDS of the block-wide merges (in the waves' scratch).
+struct LoopSelect {
+    uint32_t hist[256];
+    uint64_t kmin, kmax;
+    int sel_digit, sel_count, need, kept, evicted, taken;
+};
+
+// The whole block merges expert e's n bids into its h holders, for the
+// expert with more bids or holders than one wave takes: an MSD radix select
+// of the C-th largest key over for_bids (all of the expert's bids, a call
+// fn(position, key, valid) with wave-uniform trips) and the holder table.
+// The kept keys go to the other holder table, the displaced holders first to
+// the expert's bucket, then to the out positions of the kept bids.
+template <class M, class F>
+__device__ __attribute__((always_inline)) inline void loop_update_block(const Ctx<M> &c, int e, int n, int *hc, int *hs, int *out,
+                                  LoopSelect &sm, F for_bids) {
+    using value_t = typename M::value_t;
+    const int tid = threadIdx.x;
+    const int C = c.C;
+    const int h = *hc, sel = *hs;
+    uint64_t *hold = c.holders + (int64_t)sel * c.T + (int64_t)e * C;
+    uint64_t *alt = c.holders + (int64_t)(sel ^ 1) * c.T + (int64_t)e * C;
+    uint64_t *gone = c.bucket + (int64_t)e * c.cap;   // (cap >= C)
+    value_t *price = c.prices + e;
+    uint64_t tmin = ~0ull, tmax = 0;
+    auto range = [&](uint64_t k, bool v) {
+        if (v) {
+            tmin = k < tmin ? k : tmin;
+            tmax = k > tmax ? k : tmax;
+        }
+    };
+    auto range_done = [&]() {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const uint64_t a = __shfl_xor(tmin, off), b = __shfl_xor(tmax, off);
+            tmin = a < tmin ? a : tmin;
+            tmax = b > tmax ? b : tmax;
+        }
+        if (lane_id() == 0) {
+            atomicMin(reinterpret_cast<unsigned long long *>(&sm.kmin), (unsigned long long)tmin);
+            atomicMax(reinterpret_cast<unsigned long long *>(&sm.kmax), (unsigned long long)tmax);
+        }
+    };
+    auto for_all = [&](auto fn) {
+        for (int i = tid; i < h; i += kLoopThreads) fn(hold[i], true);
+        for_bids([&](uint32_t, uint64_t k, bool v) { fn(k, v); });
+    };
+    __syncthreads();
+    if (tid == 0) {
+        sm.kmin = ~0ull;
+        sm.kmax = 0;
+        sm.kept = sm.evicted = sm.taken = 0;
+    }
+    __syncthreads();
+    if (h + n <= C) {
+        // Room for every bid.
+        for_bids([&](uint32_t at, uint64_t k, bool v) {
+            if (!v) return;
+            const int s = h + atomicAdd(&sm.taken, 1);
+            if (s < C) hold[s] = k;
+            st_agent(&out[at], -1);
+        });
+        __syncthreads();
+        if (h + n == C) {
+            for (int i = tid; i < C; i += kLoopThreads) range(hold[i], true);
+            range_done();
+        }
+        __syncthreads();
+        if (tid == 0) {
+            *hc = h + n;
+            if (h + n == C) st_price(price, M::key_bid(sm.kmin));
+        }
+        __syncthreads();
+        return;
+    }
+    for_all(range);
+    range_done();
+    __syncthreads();
+    const uint64_t kdiff = sm.kmin ^ sm.kmax;   // non-zero: more than C distinct keys
+    const int first = kdiff ? ((63 - __clzll((long long)kdiff)) / 8) * 8 : 0;
+    uint64_t pmask = first >= 56 ? 0ull : ~0ull << (first + 8);
+    uint64_t prefix = sm.kmin & pmask;
+    int need = C;
+    bool at_min = false;
+    for (int shift = first; shift >= 0; shift -= 8) {
+        for (int i = tid; i < 256; i += kLoopThreads) sm.hist[i] = 0;
+        __syncthreads();
+        for_all([&](uint64_t k, bool v) {
+            if (v && (k & pmask) == prefix) atomicAdd(&sm.hist[(k >> shift) & 255], 1u);
+        });
+        __syncthreads();
+        pick_digit(sm, need);
+        __syncthreads();
+        prefix |= (uint64_t)sm.sel_digit << shift;
+        pmask |= 255ull << shift;
+        need = sm.need;
+        const bool whole = sm.sel_count == need;
+        __syncthreads();
+        if (whole && shift > 0) {   // the C-th largest is the lowest key of the prefix
+            at_min = true;
+            break;
+        }
+    }
+    if (at_min) {
+        if (tid == 0) sm.kmin = ~0ull;
+        __syncthreads();
+        tmin = ~0ull;
+        tmax = 0;
+        for_all([&](uint64_t k, bool v) { range(k, v && (k & pmask) == prefix); });
+        range_done();
+        __syncthreads();
+    }
+    const uint64_t kstar = at_min ? sm.kmin : prefix;   // keys are unique: a key
+    for (int i = tid; i < h; i += kLoopThreads) {
+        const uint64_t k = hold[i];
+        if (k >= kstar) {
+            const int at = atomicAdd(&sm.kept, 1);
+            if (at < C) alt[at] = k;
+        } else {
+            const int at = atomicAdd(&sm.evicted, 1);
+            if (at < c.cap) gone[at] = k;
+        }
+    }
+    __threadfence_block();
+    __syncthreads();
+    const int room = C - h, ne = sm.evicted;
+    for_bids([&](uint32_t at, uint64_t k, bool v) {
+        if (!v) return;
+        int o = key_token(k);
+        if (k >= kstar) {
+            const int w = atomicAdd(&sm.kept, 1);
+            if (w < C) alt[w] = k;
+            const int r = atomicAdd(&sm.taken, 1) - room;
+            o = r < 0 ? -1 : (r < ne && r < c.cap ? key_token(gone[r]) : -1);
+        }
+        st_agent(&out[at], o);
+    });
+    __threadfence_block();
+    __syncthreads();
+    if (tid == 0) {
+        *hc = C;
+        *hs = sel ^ 1;
+        st_price(price, M::key_bid(kstar));
+    }
+    __syncthreads();
+}
+
+// The whole block merges expert e's bids (entries of the staged list of m
+// with local expert le) into its h <= kLoopThreads holders, one per thread.
+// The threshold comes from histograms of the keys' upper words (one or two
+// for a few hundred to a few thousand keys). In place: kept bids take the
+// free slots, then the displaced holders'.
+constexpr int kLoopBins = 2 * kLoopThreads;
+struct LoopMerge {
+    union {
+        uint32_t hist[kLoopBins];      // the search
+        struct {                       // then the displaced holders and their slots
+            uint64_t gone[kLoopThreads];
+            uint16_t gslot[kLoopThreads];
+        };
+    } u;
+    uint32_t mn[kLoopWaves], mx[kLoopWaves];
+    int wsum[kLoopWaves], wcnt[2][kLoopWaves];
+    uint64_t low[kLoopWaves];
+    int bin, above, reach, evicted, taken;
+};
+static_assert(sizeof(LoopMerge) <= kLoopWaves * 2 * 64 * 8, "fits the waves' scratch");
+template <class M>
+__device__ __attribute__((always_inline)) inline void loop_update_list(
+    const Ctx<M> &c, int e, uint32_t le, int n, int *hc, int sel, int *out, const uint64_t *key,
+    const uint32_t *pos, int m, LoopMerge &sm) {
+    uint64_t *gone = sm.u.gone;
+    uint16_t *gslot = sm.u.gslot;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int C = c.C;
+    const int h = *hc;
+    uint64_t *hold = c.holders + (int64_t)sel * c.T + (int64_t)e * C;
+    const int room = C - h;
+    const int m_round = ((m + 63) / 64) * 64;   // (whole waves)
+    const uint64_t hk = tid < h ? hold[tid] : 0ull;
+    auto entry = [&](int i) -> uint64_t {
+        return i < m && (pos[i] >> 24) == le ? key[i] : 0ull;
+    };
+    uint32_t mn = ~0u, mx = 0u;
+    auto range = [&](uint64_t k) {
+        const uint32_t x = (uint32_t)(k >> 32);
+        mn = k != 0 && x < mn ? x : mn;
+        mx = k != 0 && x > mx ? x : mx;
+    };
+    range(hk);
+#pragma unroll 2
+    for (int i = tid; i < m_round; i += kLoopThreads) range(entry(i));
+    uint64_t thr = 0;
+    if (tid == 0) sm.evicted = sm.taken = 0;
+    if (n > room) {
+        mn = wave_min_u32(mn);
+        mx = ~wave_min_u32(~mx);
+        if (lane == 0) {
+            sm.mn[wave] = mn;
+            sm.mx[wave] = mx;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kLoopWaves; ++w) {
+            mn = sm.mn[w] < mn ? sm.mn[w] : mn;
+            mx = sm.mx[w] > mx ? sm.mx[w] : mx;
+        }
+        // The threshold lies between lo, which more than C keys reach, and hi,
+        // which `above` < C reach: a histogram of the keys between them over
+        // kLoopBins bins of 2^sh each, and on into the bin that holds the C-th
+        // key, until the keys from a bin's start on are exactly C.
+        uint32_t lo = mn;
+        uint64_t hi = (uint64_t)mx + 1;
+        int above = 0;
+        bool found = false;
+        while (!found && hi - lo > 1) {
+            int sh = 0;
+            while (((hi - lo - 1) >> sh) >= (uint64_t)kLoopBins) ++sh;
+#pragma unroll
+            for (int q = 0; q < kLoopBins / kLoopThreads; ++q) sm.u.hist[q * kLoopThreads + tid] = 0;
+            __syncthreads();
+            auto count = [&](uint64_t k) {
+                const uint32_t x = (uint32_t)(k >> 32);
+                if (k != 0 && x >= lo && x < hi) atomicAdd(&sm.u.hist[(x - lo) >> sh], 1u);
+            };
+            count(hk);
+            for (int i = tid; i < m; i += kLoopThreads) count(entry(i));
+            __syncthreads();
+            // Keys from the top: thread t owns the t-th highest pair of bins.
+            static_assert(kLoopBins == 2 * kLoopThreads, "two bins a thread");
+            const int b1 = kLoopBins - 1 - 2 * tid, b0 = b1 - 1;
+            const int h1 = (int)sm.u.hist[b1], h0 = (int)sm.u.hist[b0];
+            int incl = h0 + h1;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(incl, off);
+                if (lane >= off) incl += o;
+            }
+            if (lane == 63) sm.wsum[wave] = incl;
+            __syncthreads();
+            int upto = above + incl;
+            for (int w = 0; w < wave; ++w) upto += sm.wsum[w];
+            const int before = upto - h0 - h1;   // keys above this thread's bins
+            if (before < C && upto >= C) {
+                const bool first = before + h1 >= C;
+                sm.bin = first ? b1 : b0;
+                sm.above = first ? before : before + h1;
+                sm.reach = first ? before + h1 : upto;
+            }
+            __syncthreads();
+            lo += (uint32_t)sm.bin << sh;
+            hi = sh < 32 && (uint64_t)lo + (1ull << sh) < hi ? (uint64_t)lo + (1ull << sh) : hi;
+            above = sm.above;
+            found = sm.reach == C;
+            if (sh == 0) break;
+        }
+        thr = (uint64_t)lo << 32;
+        if (!found) {   // keys that agree in the upper words: bit by bit below
+            int par = 0;
+            for (int bit = 31; bit >= 0; --bit) {
+                const uint64_t trial = thr | (1ull << bit);
+                int k = __popcll(__ballot(hk >= trial));
+                for (int i = tid; i < m_round; i += kLoopThreads)
+                    k += __popcll(__ballot(entry(i) >= trial));
+                if (lane == 0) sm.wcnt[par][wave] = k;
+                __syncthreads();
+                k = 0;
+#pragma unroll
+                for (int w = 0; w < kLoopWaves; ++w) k += sm.wcnt[par][w];
+                par ^= 1;
+                if (k >= C) thr = trial;
+                if (k == C) break;
+            }
+        }
+    }
+    __syncthreads();
+    // The displaced holders, then the bids.
+    {
+        const bool leave = hk != 0 && hk < thr;
+        const uint64_t lm = __ballot(leave);
+        int at = 0;
+        if (lane == 0 && lm) at = atomicAdd(&sm.evicted, __popcll(lm));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(lm & lanemask_lt());
+        if (leave) {
+            gone[at] = hk;
+            gslot[at] = (uint16_t)tid;
+        }
+    }
+    __syncthreads();
+    const int ne = sm.evicted;
+    uint64_t low = hk != 0 && hk >= thr ? hk : ~0ull;
+#pragma unroll 1
+    for (int i = tid; i < m_round; i += kLoopThreads) {
+        const uint64_t k = entry(i);
+        const bool keep = k != 0 && k >= thr;
+        const uint64_t km = __ballot(keep);
+        int at = 0;
+        if (lane == 0 && km) at = atomicAdd(&sm.taken, __popcll(km));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(km & lanemask_lt());
+        if (k != 0) {
+            int o = key_token(k);
+            if (keep) {
+                const int g = at - room;
+                int slot = h + at;
+                o = -1;
+                if (g >= 0 && g < ne) {
+                    slot = gslot[g];
+                    o = key_token(gone[g]);
+                }
+                if (slot < C) hold[slot] = k;
+                low = k < low ? k : low;
+            }
+            st_agent(&out[pos[i] & 0xffffffu], o);
+        }
+    }
+    low = wave_min_u64(low);
+    if (lane == 0) sm.low[wave] = low;
+    __syncthreads();
+    if (tid == 0) {
+        const int h1 = n < room ? h + n : C;
+        *hc = h1;
+        if (h1 == C) {   // full: the price is the lowest held bid
+#pragma unroll
+            for (int w = 0; w < kLoopWaves; ++w) low = sm.low[w] < low ? sm.low[w] : low;
+            st_price(c.prices + e, M::key_bid(low));
+        }
+    }
+    __syncthreads();
+}
+
+// NQ: holders of an expert per lane of a wave (C <= 64 NQ); 0: experts of more
+// than kLoopThreads tokens, merged by loop_update_block.
+// `free_rounds`: the launch's first rounds that do not look at max_rounds
+// (the rounds a phase's first launches always run).
+template <class M, int G, int NQ>
+__global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, int max_wide,
+                                                                  int free_rounds,
+                                                                  int32_t max_rounds,
+                                                                  uint32_t poll_limit) {
     const Ctx<M> c = c0.at(blockIdx.y);
     using value_t = typename M::value_t;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    value_t *pr = reinterpret_cast<value_t *>(smem_raw);
-    __shared__ UpdateSmem sm;
-    __shared__ int st_go, st_cur, st_all, st_n;
+    const int nb = gridDim.x, blk = blockIdx.x;
+    const LoopLds L = loop_lds(c.E, (int)sizeof(value_t), nb);
+    value_t *pr = reinterpret_cast<value_t *>(smem_raw + L.pr);
+    int *hc = reinterpret_cast<int *>(smem_raw + L.hc);
+    int *hs = reinterpret_cast<int *>(smem_raw + L.hs);
+    int *lec = reinterpret_cast<int *>(smem_raw + L.lec);
+    int *cnt = reinterpret_cast<int *>(smem_raw + L.cnt);
+    int *ltok = reinterpret_cast<int *>(smem_raw + L.toks);
+    uint16_t *und = reinterpret_cast<uint16_t *>(smem_raw + L.und);
+    uint64_t *key = reinterpret_cast<uint64_t *>(smem_raw + L.key);
+    uint32_t *pos = reinterpret_cast<uint32_t *>(smem_raw + L.pos);
+    LoopSelect &sel = *reinterpret_cast<LoopSelect *>(smem_raw + L.scr);
+    LoopMerge &merge = *reinterpret_cast<LoopMerge *>(smem_raw + L.scr);
+    __shared__ int st_go, st_cur, st_all, st_n, st_rounds, s_m, s_pack, s_out, s_err, s_max, s_sum,
+        s_und;
     SolveCtrl *ctrl = c.ctrl;
     const int tid = threadIdx.x;
-    const BidSmem B = bid_smem(c.E, (int)sizeof(value_t));
-    int *lcnt = reinterpret_cast<int *>(smem_raw + B.lcnt);
-    for (int e = tid; e < c.E; e += kThreads) lcnt[e] = 0;
-    uint64_t target = 0;
-    for (int r = 0; r < max_wide; ++r) {
-        if (tid == 0) {
-            const int done = ld_relaxed(&ctrl->done);
-            const int cur = ld_relaxed(&ctrl->cur) & 1;
-            const int all = ld_relaxed(&ctrl->all_active);
-            const int n = all ? c.T : ld_relaxed(&ctrl->active_count[cur]);
-            st_go = !done && n > 0 && (all || n > c.engine_cap) &&
-                    ld_relaxed(&ctrl->rounds) < max_rounds && !ld_relaxed(&ctrl->internal_error);
-            st_cur = cur;
-            st_all = all;
-            st_n = n;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    uint64_t *scr = reinterpret_cast<uint64_t *>(smem_raw + L.scr) + wave * 2 * 64;
+    if (tid == 0) {
+        const int cur = ctrl->cur & 1;
+        const int all = ctrl->all_active;
+        const int n = all ? c.T : ctrl->active_count[cur];
+        st_rounds = ctrl->rounds;
+        st_go = !ctrl->done && !ctrl->internal_error && n > 0 && n <= c.T &&
+                (all || n > c.engine_cap) && (free_rounds > 0 || st_rounds < max_rounds);
+        st_cur = cur;
+        st_all = all;
+        st_n = n;
+        s_err = 0;
+    }
+    __syncthreads();
+    if (!st_go) return;
+    const bool last_phase = ctrl->last_phase != 0;
+    const bool early_ok = ctrl->early_ok != 0;
+    const value_t eps = (value_t)ctrl->eps;
+    // Positions: a multiple of eight per block (the scans read eight bytes:
+    // eight experts of one byte, or four of two with more than 256 experts).
+    const int per = ((st_n + nb - 1) / nb + 7) & ~7;
+    const bool narrow = c.E <= 256;
+    const int epl = narrow ? 8 : 4, ebits = narrow ? 8 : 16;
+    const uint32_t emask = narrow ? 0xffu : 0xffffu;
+    const int64_t base = (int64_t)blk * per;
+    const bool in_lds = per <= kLoopToks;
+    const int pe = (c.E + nb - 1) / nb;
+    const int e_lo = blk * pe;
+    const int owned = e_lo >= c.E ? 0 : (c.E - e_lo < pe ? c.E - e_lo : pe);
+    unsigned char *bexp = reinterpret_cast<unsigned char *>(c.ovf_exp);
+    uint64_t *bkey = c.ovf_key;
+    int *mine = c.active + (int64_t)(st_cur ^ 1) * c.T;   // this block's tokens, packed (own positions)
+    int *out = c.active + (int64_t)st_cur * c.T;          // read as the entry list first
+    int m = 0;   // this block's active tokens
+    if (base < st_n) m = (int)(st_n - base < per ? st_n - base : per);
+    for (int j = tid; j < m; j += kLoopThreads) {
+        int t = st_all ? (int)base + j : out[base + j];
+        if (t < 0 || t >= c.T) {
+            flag_internal(ctrl);
+            s_err = 1;
+            t = 0;
+        }
+        if (in_lds) ltok[j] = t;
+        else mine[base + j] = t;
+    }
+    for (int i = tid; i < owned; i += kLoopThreads) {
+        int h = c.hcount[e_lo + i];
+        int sl = c.hsel[e_lo + i];
+        if (h < 0 || h > c.C || (sl & ~1)) {
+            flag_internal(ctrl);
+            s_err = 1;
+            h = h < 0 ? 0 : (h > c.C ? c.C : h);
+        }
+        hc[i] = h;
+        hs[i] = sl & 1;
+    }
+    const int gl = lane & (G - 1);
+    int n = st_n;
+    int rounds = 0;
+    uint32_t seq = 0;
+    unsigned long long bids = 0;
+    bool early = false;
+    for (;;) {
+        // (1) This block's bids against the prices at the start of the round.
+        for (int e = tid; e < c.E; e += kLoopThreads) pr[e] = ld_price(c.prices + e);
+        for (int i = tid; i < owned; i += kLoopThreads) lec[i] = 0;
+        if (tid == 0) s_m = s_pack = s_out = s_und = 0;
+        __syncthreads();
+        value_t pmin = pr[0];
+        if (m > 0) {
+            for (int e = lane; e < c.E; e += 64) pmin = pr[e] < pmin ? pr[e] : pmin;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const value_t o = __shfl_xor(pmin, off);
+                pmin = o < pmin ? o : pmin;
+            }
+        }
+        auto place = [&](int j, int t, typename M::value_t v2, int e1, typename M::value_t s1) {
+            if (e1 >= c.E) {   // every value non-finite: any expert, the bid overflows
+                e1 = 0;
+                s1 = 0;   // with v2 = -inf the bid is +inf: overflow is flagged
+            }
+            const value_t bid = (c.E > 1) ? (value_t)((s1 - v2) + eps) : (value_t)(s1 + eps);
+            int overflow = 0;
+            const uint64_t k = M::make_key(bid, t, &overflow);
+            if (overflow) ctrl->overflow = 1;
+            st_agent(&bkey[base + j], k);
+            if (narrow) st_agent(reinterpret_cast<uint8_t *>(bexp) + base + j, (uint8_t)e1);
+            else st_agent(reinterpret_cast<uint16_t *>(bexp) + base + j, (uint16_t)e1);
+        };
+        for (int jb = 0; jb < m; jb += kLoopToks) {
+            const int jn = m - jb < kLoopToks ? m - jb : kLoopToks;
+            // Eight lanes per token take the summaries (four in flight); the
+            // tokens a summary cannot decide are left for the rows below.
+            int nu = jn;
+            if constexpr (G >= 8) {
+                constexpr int kG8 = kLoopThreads / 8;
+                const int g8 = lane & 7;
+                const int r8 = ((jn + 7) / 8) * 8;   // (whole waves)
+                for (int j0 = tid / 8; j0 < r8; j0 += kG8 * kBidRows) {
+                    uint32_t sw[kBidRows][4];
+                    int toks[kBidRows];
+#pragma unroll
+                    for (int u = 0; u < kBidRows; ++u) {
+                        const int j = j0 + u * kG8;
+                        toks[u] = j < jn ? (in_lds ? ltok[jb + j] : mine[base + jb + j]) : 0;
+                        sw[u][0] = sw[u][1] = sw[u][2] = sw[u][3] = 0;
+                        if (j < jn) load_summary(c.sums, toks[u], g8, sw[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < kBidRows; ++u) {
+                        const int j = j0 + u * kG8;
+                        const bool valid = j < jn;
+                        if (__ballot(valid) == 0) break;
+                        value_t v1, v2, s1;
+                        int e1;
+                        const bool exact =
+                            top2_entries<M>(c, sw[u], valid, g8, pr, pmin, v1, e1, v2, s1);
+                        if (valid && g8 == 0) {
+                            if (exact) place(jb + j, toks[u], v2, e1, s1);
+                            else und[atomicAdd(&s_und, 1)] = (uint16_t)j;
+                        }
+                    }
+                }
+                __syncthreads();
+                nu = s_und;
+            }
+            // Whole rows, G lanes per token, two rows in flight.
+            constexpr int kGroups = kLoopThreads / G;
+            constexpr int kRows = 2;
+            const int per_wave = 64 / G;
+            const int ru = ((nu + per_wave - 1) / per_wave) * per_wave;
+            for (int j0 = tid / G; j0 < ru; j0 += kGroups * kRows) {
+                int js[kRows], toks[kRows];
+                value_t sv[kRows][8];
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) {
+                    const int i = j0 + u * kGroups;
+                    js[u] = i < nu ? jb + (G >= 8 ? (int)und[i] : i) : -1;
+                    toks[u] = js[u] >= 0 ? (in_lds ? ltok[js[u]] : mine[base + js[u]]) : 0;
+                    if (js[u] >= 0 && 8 * gl < c.E && c.E <= 8 * G)
+                        load8<M>(c.S, (int64_t)toks[u] * c.E, 8 * gl, c.E, c.scale, sv[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) {
+                    const bool valid = js[u] >= 0;
+                    if (__ballot(valid) == 0) break;
+                    value_t v1, v2, s1;
+                    int e1;
+                    if (c.E <= 8 * G)
+                        top2_row<M, G>(sv[u], 8 * gl, c.E, valid, pr, v1, e1, v2, s1);
+                    else
+                        top2_token<M, G>(c, toks[u], valid, pr, v1, e1, v2, s1);
+                    if (valid && gl == 0) place(js[u], toks[u], v2, e1, s1);
+                }
+            }
+            if (jb + kLoopToks < m) {
+                __syncthreads();
+                if (tid == 0) s_und = 0;
+                __syncthreads();
+            }
+        }
+        ++seq;
+        if (!loop_barrier(c.flags, seq, nb, (uint32_t)m | (s_err ? kLoopErr : 0u), cnt, ctrl,
+                          poll_limit))
+            return;
+        // (2) The bids of this block's experts: the filled positions of every
+        // block.
+        if (tid < 64) {
+            const uint32_t a = (uint32_t)cnt[lane], b = (uint32_t)cnt[lane + 64];
+            const uint32_t mx = ~wave_min_u32(~((a > b ? a : b) & ~kLoopErr));
+            if (lane == 0) s_max = (int)mx < per ? (int)mx : per;
+            if (__ballot(((a | b) & kLoopErr) != 0) != 0 && lane == 0) s_err = 2;
         }
         __syncthreads();
-        if (!st_go) break;
-        for (int e = tid; e < c.E; e += kThreads) pr[e] = c.prices[e];
+        if (s_err == 2) return;   // (every block saw the same words)
+        // Scan index k covers epl positions of block k >> sh (a power of two
+        // of chunks per block; those past its filled positions are empty).
+        int sh = 0;
+        while (epl << sh < s_max) ++sh;
+        const int total = owned > 0 ? nb << sh : 0;
+        auto chunk_at = [&](int k, int &at, int &left) {
+            left = 0;
+            at = 0;
+            if (k >= total) return;
+            const int tile = k >> sh, ch = k & ((1 << sh) - 1);
+            left = (cnt[tile] < per ? cnt[tile] : per) - epl * ch;
+            left = left < epl ? left : epl;
+            at = tile * per + epl * ch;
+        };
+        auto load_chunk = [&](int k, int &at, int &left) -> uint64_t {
+            chunk_at(k, at, left);
+            if (left <= 0) return 0;
+            return ld_agent(reinterpret_cast<const uint64_t *>(bexp + (narrow ? at : 2 * at)));
+        };
+        // Collects the chunk's bids for this block's experts.
+        auto take_chunk = [&](uint64_t w, int at, int left) {
+            uint32_t hit = 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const uint32_t i = ((uint32_t)(w >> ((ebits * q) & 63)) & emask) - (uint32_t)e_lo;
+                hit |= (uint32_t)(i < (uint32_t)owned && q < left) << q;
+            }
+            if (hit == 0) return;
+            int f = atomicAdd(&s_m, __popc(hit));
+            for (; hit != 0; hit &= hit - 1) {
+                const int q = __ffs((int)hit) - 1;
+                const int i = (int)((uint32_t)(w >> (ebits * q)) & emask) - e_lo;
+                if (f < L.cap) pos[f] = (uint32_t)(at + q) | ((uint32_t)i << 24);
+                ++f;
+                atomicAdd(&lec[i], 1);
+            }
+        };
+        constexpr int kU = 8;
+        for (int k0 = 0; k0 < total; k0 += kU * kLoopThreads) {
+            uint64_t w[kU];
+            int at, left;
+#pragma unroll
+            for (int u = 0; u < kU; ++u) w[u] = load_chunk(k0 + u * kLoopThreads + tid, at, left);
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                if (k0 + u * kLoopThreads >= total) break;
+                chunk_at(k0 + u * kLoopThreads + tid, at, left);
+                take_chunk(w[u], at, left);
+            }
+        }
         __syncthreads();
-        const value_t eps = (value_t)ctrl->eps;
-        const value_t pmin = block_min_price<M>(pr, c.E);
-        for (int i0 = blockIdx.x * kBidTile; i0 < st_n; i0 += gridDim.x * kBidTile)
-            bid_block<M, G>(c, i0, i0 + kBidTile < st_n ? i0 + kBidTile : st_n, st_all != 0,
-                            c.active + (int64_t)st_cur * c.T, eps, pr, pmin, lcnt,
-                            reinterpret_cast<uint64_t *>(smem_raw + B.lkey),
-                            reinterpret_cast<int *>(smem_raw + B.lexp),
-                            reinterpret_cast<int *>(smem_raw + B.lrank));
-        target += gridDim.x;
-        if (!grid_barrier(c.bar, target, ctrl, poll_limit)) return;
-        const int novf = min(ld_relaxed(c.ovf_count), c.T);
-        for (int e = blockIdx.x; e < c.E; e += gridDim.x) update_expert<M>(c, e, st_cur ^ 1, novf, sm);
-        target += gridDim.x;
-        if (!grid_barrier_last(c.bar, target, ctrl, poll_limit, [&]() { end_round<M>(c); }))
-            return;
+        // (3) Merge the collected bids.
+        if constexpr (NQ > 0) {
+            // An expert per wave, or the block for those with many bids.
+            // More bids than the list holds: a chunk per thread at a time (at
+            // most 8 kLoopThreads bids), each merged before the next.
+            static_assert(8 * kLoopThreads <= kLoopCandMin, "one step fits the list");
+            const bool over = s_m > L.cap;
+            for (int k0 = 0;; k0 += kLoopThreads) {
+                if (over) {
+                    __syncthreads();
+                    if (tid == 0) s_m = 0;
+                    for (int i = tid; i < owned; i += kLoopThreads) lec[i] = 0;
+                    __syncthreads();
+                    int at, left;
+                    const uint64_t w = load_chunk(k0 + tid, at, left);
+                    take_chunk(w, at, left);
+                    __syncthreads();
+                }
+                const int mt = s_m;
+                for (int i = tid; i < mt; i += kLoopThreads)
+                    key[i] = ld_agent(&bkey[pos[i] & 0xffffffu]);
+                for (int i0 = 0; i0 < owned; i0 += kLoopWaves) {
+                    const int i = i0 + wave;
+                    const bool take = i < owned && lec[i] > 0 && lec[i] <= kLoopWaveBids;
+                    uint64_t kk[NQ];
+                    uint64_t *hold = nullptr;
+                    int h = 0;
+                    if (take) {
+                        h = hc[i];
+                        hold = c.holders + (int64_t)hs[i] * c.T + (int64_t)(e_lo + i) * c.C;
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) {
+                            const int s = 64 * q + lane;
+                            kk[q] = s < h ? hold[s] : 0;
+                        }
+                    }
+                    if (i0 == 0) __syncthreads();   // the keys
+                    if (take) {
+                        const int h1 = loop_update_wave<M, NQ>(c, kk, h, hold, (uint32_t)i, key, pos,
+                                                           mt, out, scr, scr + 64);
+                        if (h1 == c.C) {   // full: the price is the lowest held bid
+                            uint64_t lowest = ~0ull;
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q)
+                                if (kk[q] != 0 && kk[q] < lowest) lowest = kk[q];
+                            lowest = wave_min_u64(lowest);
+                            if (lane == 0) st_price(c.prices + e_lo + i, M::key_bid(lowest));
+                        }
+                        if (lane == 0) {
+                            hc[i] = h1;
+                            atomicAdd(&s_out, lec[i] - (h1 - h));
+                        }
+                    }
+                }
+                __syncthreads();
+                for (int i = 0; i < owned; ++i) {
+                    const int ne = lec[i];
+                    if (ne <= kLoopWaveBids) continue;
+                    const int h = hc[i];
+                    loop_update_list<M>(c, e_lo + i, (uint32_t)i, ne, &hc[i], hs[i], out, key, pos,
+                                        mt, merge);
+                    if (tid == 0) s_out += ne - (hc[i] - h);
+                    __syncthreads();
+                }
+                if (!over || k0 + kLoopThreads >= total) break;
+            }
+        } else {
+            for (int i = 0; i < owned; ++i) {
+                const int ne = lec[i];
+                if (ne == 0) continue;
+                const int e = e_lo + i;
+                const int h = hc[i];
+                loop_update_block<M>(c, e, ne, &hc[i], &hs[i], out, sel, [&](auto fn) {
+                    for (int k = tid; k < total; k += kLoopThreads) {
+                        int at, left;
+                        const uint64_t w = load_chunk(k, at, left);
+                        for (int q = 0; q < left; ++q)
+                            if ((int)((uint32_t)(w >> (ebits * q)) & emask) == e)
+                                fn((uint32_t)(at + q), ld_agent(&bkey[at + q]), true);
+                    }
+                });
+                if (tid == 0) s_out += ne - (hc[i] - h);
+                __syncthreads();
+            }
+        }
+        ++seq;
+        if (!loop_barrier(c.flags, seq, nb, (uint32_t)s_out, cnt, ctrl, poll_limit)) return;
+        if (tid < 64) {
+            int v = cnt[lane] + cnt[lane + 64];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+            if (lane == 0) s_sum = v;
+        }
+        __syncthreads();
+        // (4) The round is closed (see end_round); this block's tokens for the next.
+        bids += (unsigned long long)n;
+        ++rounds;
+        n = s_sum;
+        const int m_old = m;
+        for (int j0 = 0; j0 < m_old; j0 += kLoopThreads) {
+            // (a pass reads its positions before any of it is packed over them)
+            const int j = j0 + tid;
+            int t = j < m_old ? ld_agent(&out[base + j]) : -1;
+            if (t >= c.T) {
+                flag_internal(ctrl);
+                s_err = 1;
+                t = -1;
+            }
+            const uint64_t mask = __ballot(t >= 0);
+            int at = 0;
+            if (lane == 0 && mask) at = atomicAdd(&s_pack, __popcll(mask));
+            at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & lanemask_lt());
+            if (t >= 0) {
+                if (in_lds) ltok[at] = t;
+                else mine[base + at] = t;
+            }
+        }
+        __syncthreads();
+        m = s_pack;
+        early = n > 0 && c.early_n != 0 && !last_phase &&
+                n <= (c.early_n > 0 ? c.early_n : -c.early_n) && (c.early_n < 0 || early_ok);
+        if (n == 0 || early || n <= c.engine_cap || rounds >= max_wide ||
+            (rounds >= free_rounds && st_rounds + rounds >= max_rounds))
+            break;
+        __syncthreads();
+    }
+    // Hand the state back: the holder counts, the active tokens as one list.
+    for (int i = tid; i < owned; i += kLoopThreads) {
+        c.hcount[e_lo + i] = hc[i];
+        c.hsel[e_lo + i] = hs[i];
+    }
+    if (n > 0 && !early) {
+        ++seq;
+        if (!loop_barrier(c.flags, seq, nb, (uint32_t)m, cnt, ctrl, poll_limit)) return;
+        if (tid < 64) {
+            int before = 0;
+            if (lane < blk) before += cnt[lane];
+            if (lane + 64 < blk) before += cnt[lane + 64];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+            if (lane == 0) s_sum = before;
+        }
+        __syncthreads();
+        const int before = s_sum;
+        for (int j = tid; j < m; j += kLoopThreads) {
+            const int t = in_lds ? ltok[j] : mine[base + j];
+            if (before + j < c.T) out[before + j] = t;
+        }
+    }
+    if (blk == 0 && tid == 0) {
+        ctrl->bids += bids;
+        ctrl->rounds = st_rounds + rounds;
+        ctrl->cur = st_cur;
+        ctrl->active_count[st_cur] = early ? 0 : n;
+        ctrl->active_count[st_cur ^ 1] = 0;
+        ctrl->all_active = 0;
+        ctrl->pad0 = 0;
+        if (early) ctrl->skip_check = 1;
+        if (n == 0 && last_phase) ctrl->done = 1;
     }
 }
 
@@ -5090,22 +6047,29 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     const int bid_blocks = (int)((c.T + kBidTile - 1) / kBidTile);   // one tile of the list each
     const size_t bid_bytes = bid_smem(c.E, (int)sizeof(value_t)).total;
     int upd_blocks = c.E < 2048 ? c.E : 2048;
-    // Round loop for phases that stay large: one block per compute unit,
-    // shared out among the problems of a batch (every block of the grid must
-    // be resident at once; a batch larger than the device holds skips it).
-    // A single problem takes half the units: its grid barriers cost less
-    // (1% faster over eight workloads; batches of 64 and 128 problems were
-    // slower with half).
+    // Round loop (every block of the grid must be resident at once): half the
+    // compute units for a single problem, a share of them for a batch's
+    // (a batch larger than the device holds skips it).
     int coop_blocks = 0;
+    size_t loop_bytes = 0;
+    const auto loop_fn = c.C <= 256 ? &round_loop_kernel<M, G, 4>
+                         : c.C <= kLoopThreads ? &round_loop_kernel<M, G, kLoopThreads / 64>
+                                               : &round_loop_kernel<M, G, 0>;
     {
         const int cus = facts.cus;
-        const int per_cu =
-            cus > 0 ? occupancy(dev, reinterpret_cast<const void *>(&wide_loop_kernel<M, G>),
-                                kThreads, bid_bytes)
-                    : 0;
-        if (per_cu > 0 && cus > 0) {
-            coop_blocks = B == 1 ? cus / 2 : cus / B;
-            if (coop_blocks == 0 && B <= cus * per_cu) coop_blocks = 1;
+        const void *fn = reinterpret_cast<const void *>(loop_fn);
+        int nb = cus <= 0 ? 0 : (B == 1 ? cus / 2 : cus / B);
+        if (nb > kLoopMaxBlocks) nb = kLoopMaxBlocks;
+        if (nb == 0 && cus > 0) nb = 1;
+        if (nb > 0 && (c.E + nb - 1) / nb <= kLoopOwned) {
+            loop_bytes = loop_lds(c.E, (int)sizeof(value_t), nb).total;
+            if (lds_optin(dev, fn, loop_bytes) == hipSuccess) {
+                const int per_cu = occupancy(dev, fn, kLoopThreads, loop_bytes);
+                if ((int64_t)nb * B <= (int64_t)cus * per_cu) coop_blocks = nb;
+            } else {
+                (void)hipGetLastError();
+                debug_note("round loop LDS opt-in refused", hipErrorInvalidValue);
+            }
         }
     }
     // Each slot: the phase start (with the decision on the previous slot's
@@ -5114,23 +6078,24 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     // engine leaves unfinished goes on in the next slot), and the check.
     const bool checks = !(p.flags & BASE_ASSIGN_FULL_SCHEDULE);
     const int check_parts = phase_check_blocks(c.T, G);
-    // From the third slot on, the round loop takes the phase's first rounds
-    // as well: those slots often come after the solve has stopped (then
-    // every launch returns at once, and fewer launches cost less), and when
-    // one runs, its first rounds cost little more in the loop.
+    // A single problem's phase runs in the round loop from its first round
+    // on; a batch's first two phases start with launched rounds, which use
+    // the whole device.
     for (int slot = 0; slot < slots; ++slot) {
         if (slot > 0)   // (the start kernel began the first phase)
             hipLaunchKernelGGL(phase_begin_kernel<M>, dim3(1, B), dim3(1024), 0, s, c, p,
                                checks ? check_parts : 0);
-        const int wr = (slot >= 2 && coop_blocks > 0) ? 0 : wide_rounds;
+        const int first = slot < 2 || coop_blocks == 0 ? wide_rounds : 0;
+        const int wr = B == 1 && coop_blocks > 0 ? 0 : first;
         for (int r = 0; r < wr; ++r) {
             hipLaunchKernelGGL((bid_wide_kernel<M, G>), dim3(bid_blocks, B), dim3(kThreads),
                                bid_bytes, s, c);
             hipLaunchKernelGGL(update_wide_kernel<M>, dim3(upd_blocks, B), dim3(kThreads), 0, s, c);
         }
         if (coop_blocks > 0)
-            hipLaunchKernelGGL((wide_loop_kernel<M, G>), dim3(coop_blocks, B), dim3(kThreads),
-                               bid_bytes, s, c, kWideLoopRounds, p.max_rounds, barrier_polls());
+            hipLaunchKernelGGL(loop_fn, dim3(coop_blocks, B), dim3(kLoopThreads), loop_bytes, s, c,
+                               kWideLoopRounds + (first - wr), first - wr, p.max_rounds,
+                               barrier_polls());
         if (engine) {
             // Summary readers: multiples of 8 blocks per problem, 256 in all
             // when one problem.

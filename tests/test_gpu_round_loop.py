@@ -1,0 +1,62 @@
+"""The grid-wide round loop at the edges of its branches: holders per lane
+(C up to 256, up to 512, above), experts merged by one wave or by the block,
+more bids for a block's experts than its list holds, one- and two-byte expert
+indices, several experts per block, free slots filled and holders displaced in
+one round."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2103_16716_amd as pb
+import workloads as wl
+from gpu_common import dev, eps_expected, host, rounding_slack
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "the GPU tests need an MI355X"
+    pb.lib()
+
+
+def _scores(T, E, kind, seed):
+    if kind == "int16":
+        return wl.random_scores(T, E, seed, "int16")
+    S = wl.random_scores(T, E, seed)
+    if kind == "crowd":      # every token wants the same expert first
+        S[:, E // 2] += 6.0
+    return S
+
+
+@pytest.mark.parametrize("kind", ["normal", "crowd", "int16"])
+@pytest.mark.parametrize("T,E", [(2048, 128), (2048, 8), (2044, 4), (2048, 2), (1000, 250),
+                                 (2047, 23)])
+def test_same_rounds_as_the_single_workgroup_solver(monkeypatch, T, E, kind):
+    """The single-workgroup solver runs the same rounds with code of its own:
+    assignment, sort vector, prices and round count agree bit for bit."""
+    S = dev(_scores(T, E, kind, seed=T + E))
+    res = []
+    for route in ("1", "0"):
+        monkeypatch.setenv("BASE_SMALL_PATH", route)
+        res.append(pb.assign(S))
+    for name in ("assign", "perm", "prices"):
+        np.testing.assert_array_equal(host(getattr(res[0], name)), host(getattr(res[1], name)))
+    assert (res[0].stats.rounds, res[0].stats.bids) == (res[1].stats.rounds, res[1].stats.bids)
+
+
+@pytest.mark.parametrize("T,E,kind", [(16384, 32, "crowd"), (6000, 600, "normal"),
+                                      (6000, 600, "crowd"), (12288, 8, "crowd"),
+                                      (4097, 17, "crowd")])
+def test_optimality_bound(T, E, kind):
+    """Weak duality at the returned prices certifies the bound, whatever path
+    the merges took; every expert is full and perm is the stable sort."""
+    Sh = _scores(T, E, kind, seed=3 * T + E)
+    res = pb.assign(dev(Sh))
+    a, p = host(res.assign), host(res.prices).astype(np.float64)
+    assert oracle.balanced_counts_ok(a, E)
+    np.testing.assert_array_equal(host(res.perm), oracle.stable_perm(a, E))
+    S = Sh.astype(np.float64)
+    gap = oracle.dual_bound(S, p) - oracle.objective(S, a)
+    assert gap <= T * eps_expected(Sh, 1e-4) + rounding_slack(T, S, p)
