@@ -2405,7 +2405,7 @@ __device__ __attribute__((always_inline)) inline void loop_update_list(
 // than kLoopThreads tokens, merged by loop_update_block.
 // `free_rounds`: the launch's first rounds that do not look at max_rounds
 // (the rounds a phase's first launches always run).
-template <class M, int G, int NQ>
+template <class M, int G, int NQ>   // G >= 8
 __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, int max_wide,
                                                                   int free_rounds,
                                                                   int32_t max_rounds,
@@ -2526,8 +2526,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
             const int jn = m - jb < kLoopToks ? m - jb : kLoopToks;
             // Eight lanes per token take the summaries (four in flight); the
             // tokens a summary cannot decide are left for the rows below.
-            int nu = jn;
-            if constexpr (G >= 8) {
+            {
                 constexpr int kG8 = kLoopThreads / 8;
                 const int g8 = lane & 7;
                 const int r8 = ((jn + 7) / 8) * 8;   // (whole waves)
@@ -2557,8 +2556,8 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
                     }
                 }
                 __syncthreads();
-                nu = s_und;
             }
+            const int nu = s_und;
             // Whole rows, G lanes per token, two rows in flight.
             constexpr int kGroups = kLoopThreads / G;
             constexpr int kRows = 2;
@@ -2570,7 +2569,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
 #pragma unroll
                 for (int u = 0; u < kRows; ++u) {
                     const int i = j0 + u * kGroups;
-                    js[u] = i < nu ? jb + (G >= 8 ? (int)und[i] : i) : -1;
+                    js[u] = i < nu ? jb + (int)und[i] : -1;
                     toks[u] = js[u] >= 0 ? (in_lds ? ltok[js[u]] : mine[base + js[u]]) : 0;
                     if (js[u] >= 0 && 8 * gl < c.E && c.E <= 8 * G)
                         load8<M>(c.S, (int64_t)toks[u] * c.E, 8 * gl, c.E, c.scale, sv[u]);
@@ -6001,6 +6000,7 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
                     ++nslots;
                 }
             }
+            if (ssp_r == 0) nslots = 1;   // nothing hands over between launches
             for (int slot = 0; slot < nslots; ++slot) {
                 const bool last = slot == nslots - 1;
                 const int cap = (!last && ssp_r > 0) ? c.ssp_cap : 0;
@@ -6043,6 +6043,17 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
             ++slots;
         }
     }
+    // Integer mode runs from range * K / 8 down to one scaled unit, often a
+    // phase or two more: slots of their own for those, up to the widest range,
+    // without the duality check (as in the tail, which would take them
+    // otherwise: 330 us for one at T = 4096, E = 16; an empty slot costs 18).
+    int all_slots = slots;
+    if (M::kInteger && engine && p.eps_initial <= 0.0) {
+        double e = 65535.0 * (double)p.scale / 8.0;
+        int n = 1;
+        for (; e > 1.0 && n < 64; ++n) e /= p.eps_factor;
+        if (n > all_slots) all_slots = n;
+    }
     const int wide_rounds = engine ? 3 : 2;
     const int bid_blocks = (int)((c.T + kBidTile - 1) / kBidTile);   // one tile of the list each
     const size_t bid_bytes = bid_smem(c.E, (int)sizeof(value_t)).total;
@@ -6052,9 +6063,10 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     // (a batch larger than the device holds skips it).
     int coop_blocks = 0;
     size_t loop_bytes = 0;
-    const auto loop_fn = c.C <= 256 ? &round_loop_kernel<M, G, 4>
-                         : c.C <= kLoopThreads ? &round_loop_kernel<M, G, kLoopThreads / 64>
-                                               : &round_loop_kernel<M, G, 0>;
+    constexpr int GL = G < 8 ? 8 : G;   // (its lanes per row: a summary takes eight)
+    const auto loop_fn = c.C <= 256 ? &round_loop_kernel<M, GL, 4>
+                         : c.C <= kLoopThreads ? &round_loop_kernel<M, GL, kLoopThreads / 64>
+                                               : &round_loop_kernel<M, GL, 0>;
     {
         const int cus = facts.cus;
         const void *fn = reinterpret_cast<const void *>(loop_fn);
@@ -6081,10 +6093,10 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     // A single problem's phase runs in the round loop from its first round
     // on; a batch's first two phases start with launched rounds, which use
     // the whole device.
-    for (int slot = 0; slot < slots; ++slot) {
+    for (int slot = 0; slot < all_slots; ++slot) {
         if (slot > 0)   // (the start kernel began the first phase)
             hipLaunchKernelGGL(phase_begin_kernel<M>, dim3(1, B), dim3(1024), 0, s, c, p,
-                               checks ? check_parts : 0);
+                               checks && slot < slots ? check_parts : 0);
         const int first = slot < 2 || coop_blocks == 0 ? wide_rounds : 0;
         const int wr = B == 1 && coop_blocks > 0 ? 0 : first;
         for (int r = 0; r < wr; ++r) {
@@ -6115,9 +6127,9 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
                 launch_ssp<M>(c, B, ssp_r, ssp_bytes, s);
             }
         }
-        if (!engine || slot == slots - 1)
+        if (!engine || slot == all_slots - 1)
             hipLaunchKernelGGL((tail_kernel<M, G>), dim3(1, B), dim3(kThreads), tail_smem, s, c,
-                               p, slot == slots - 1 ? 1 : 0);
+                               p, slot == all_slots - 1 ? 1 : 0);
         if (checks && slot < slots - 1) {
             const hipError_t err = launch_phase_check<M, G>(c, B, s);
             if (err != hipSuccess) return err;

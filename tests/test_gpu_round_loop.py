@@ -35,12 +35,15 @@ def _scores(T, E, kind, seed):
                                  (2047, 23)])
 def test_same_rounds_as_the_single_workgroup_solver(monkeypatch, T, E, kind):
     """The single-workgroup solver runs the same rounds with code of its own:
-    assignment, sort vector, prices and round count agree bit for bit."""
+    assignment, sort vector, prices and round count agree bit for bit. (Without
+    early phase ends, which the two routes take at different rounds; integer
+    solves without the duality checks, which the routes make in other phases.)"""
+    monkeypatch.setenv("BASE_EARLY_END_DIV", "0")
     S = dev(_scores(T, E, kind, seed=T + E))
     res = []
     for route in ("1", "0"):
         monkeypatch.setenv("BASE_SMALL_PATH", route)
-        res.append(pb.assign(S))
+        res.append(pb.assign(S, flags=pb.BASE_ASSIGN_FULL_SCHEDULE if kind == "int16" else 0))
     for name in ("assign", "perm", "prices"):
         np.testing.assert_array_equal(host(getattr(res[0], name)), host(getattr(res[1], name)))
     assert (res[0].stats.rounds, res[0].stats.bids) == (res[1].stats.rounds, res[1].stats.bids)
