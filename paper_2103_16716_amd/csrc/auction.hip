@@ -504,9 +504,11 @@ __device__ inline void top2_token(const Ctx<M> &c, int t, bool valid, const type
 // ---------------------------------------------------------- score summaries --
 //
 // A token's summary is 64 bytes: its 8 highest scores (words 0..7, fp32 bits or
-// the raw int16 score), their experts (words 8..11, two uint16 per word), the
-// 9th highest score (word 12; the lowest value when E <= 8, where the 8 cover
-// every expert) and the number of entries (word 13). Scores never change
+// the raw int16 score, in any order), their experts (words 8..11, two uint16
+// per word), a bound no other score exceeds, the 9th highest or just above it
+// (word 12; the lowest value when E <= 8, where the 8 cover every expert) and
+// the number of entries (word 13). Scores that agree in the bits the selection
+// below compares may change places at its end; the bound covers that. Scores never change
 // during a solve, so the summaries are built once. For prices p, every expert
 // outside a summary has S[t,e] - p[e] <= bound - min_e p[e]; a top-2 taken
 // over the summary is therefore the top-2 over all experts whenever its best
@@ -575,9 +577,113 @@ __device__ inline void init_problem(SolveCtrl *ctrl, void *prices, int E, const 
     }
 }
 
+// Order-preserving 32-bit images of experts [e0, e0 + 8) of a row.
+template <class M>
+__device__ inline void load8_ord(const typename M::score_t *S, int64_t base, int e0, int E,
+                                 uint32_t (&o)[8]) {
+    if constexpr (M::kInteger) {
+        if (e0 + 8 <= E && ((base + e0) & 7) == 0) {
+            const uint4 a = *reinterpret_cast<const uint4 *>(S + base + e0);
+            const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                o[j] = (uint32_t)(int32_t)(int16_t)(uint16_t)(w[j >> 1] >> (16 * (j & 1)));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = e0 + j < E ? (uint32_t)(int32_t)S[base + e0 + j] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] ^= 0x80000000u;
+    } else {
+        float f[8];
+        load8<M>(S, base, e0, E, 1, f);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = f32_ord(f[j]);
+    }
+}
+
+// Maximum over a group of G lanes.
+template <int G>
+__device__ __attribute__((always_inline)) inline uint32_t group_max_u32(uint32_t v) {
+    uint32_t x;
+    if constexpr (G > 1) { x = grp_partner<1>(v); v = x > v ? x : v; }
+    if constexpr (G > 2) { x = grp_partner<2>(v); v = x > v ? x : v; }
+    if constexpr (G > 4) { x = grp_partner<4>(v); v = x > v ? x : v; }
+    if constexpr (G > 8) { x = grp_partner<8>(v); v = x > v ? x : v; }
+    if constexpr (G > 16) { x = grp_partner<16>(v); v = x > v ? x : v; }
+    if constexpr (G > 32) { x = grp_partner<32>(v); v = x > v ? x : v; }
+    return v;
+}
+
+// The summary of token t (a group of G >= 8 lanes, 8 < E <= 8 G, lane gl's
+// images in o, valid: t < T). Bound by instructions, so the selection runs on
+// 32-bit keys: the image with its low bits replaced by the expert (the lower
+// expert higher), one max or min per comparison. Each lane sorts its eight
+// keys (a network of 19 comparators); nine rounds take the highest head of
+// the group and the lane that owned it moves on. The lanes then read the
+// chosen scores back by their experts. The bound is the 9th key with its low
+// bits set, at or above every score left out. (Nine rounds of a maximum over
+// all scores with their experts took about twice the time: 256 problems of T =
+// 2048, E = 128 are solved 110 us sooner, T = 65536, E = 256 37 us.)
+template <class M, int G>
+__device__ __attribute__((always_inline)) inline void build_summary(const Ctx<M> &c, int t,
+                                                                    bool valid, int gl,
+                                                                    const uint32_t (&o)[8]) {
+    constexpr uint32_t kMask = 8 * G - 1;
+    uint32_t k[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int e = 8 * gl + q;
+        uint32_t img = o[q];
+        if constexpr (M::kInteger) img = (img - 0x7fff8000u) << 16;   // sixteen bits of image
+        k[q] = valid && e < c.E ? (img & ~kMask) | (kMask - (uint32_t)e) : 0u;
+    }
+    auto cx = [&](int i, int j) {
+        const uint32_t a = k[i], b = k[j];
+        k[i] = a > b ? a : b;
+        k[j] = a > b ? b : a;
+    };
+    cx(0, 1); cx(2, 3); cx(4, 5); cx(6, 7);
+    cx(0, 2); cx(1, 3); cx(4, 6); cx(5, 7);
+    cx(1, 2); cx(5, 6); cx(0, 4); cx(3, 7);
+    cx(1, 5); cx(2, 6);
+    cx(1, 4); cx(3, 6);
+    cx(2, 4); cx(3, 5);
+    cx(3, 4);
+    uint32_t mine = 0, ninth = 0;
+#pragma unroll
+    for (int r = 0; r < 9; ++r) {
+        const uint32_t m = group_max_u32<G>(k[0]);
+        if (r == 8) {
+            ninth = m;
+        } else {
+            mine = gl == r ? m : mine;
+            const bool own = k[0] == m;
+#pragma unroll
+            for (int q = 0; q < 7; ++q) k[q] = own ? k[q + 1] : k[q];
+            k[7] = own ? 0u : k[7];
+        }
+    }
+    const uint32_t e = kMask - (mine & kMask);
+    const uint32_t other = grp_partner<1>(e);
+    if (!valid || gl >= 8) return;
+    uint32_t *out = c.sums + (int64_t)t * kSumWords;
+    const uint32_t ec = e < (uint32_t)c.E ? e : 0u;
+    if constexpr (M::kInteger) out[gl] = (uint32_t)(int32_t)c.S[(int64_t)t * c.E + ec];
+    else out[gl] = __float_as_uint(c.S[(int64_t)t * c.E + ec]);
+    if ((gl & 1) == 0) out[8 + (gl >> 1)] = (e & 0xffffu) | (other << 16);
+    if (gl == 0) {
+        const uint32_t top = ninth | kMask;
+        uint32_t bound;
+        if constexpr (M::kInteger) bound = (uint32_t)((int32_t)(top >> 16) - 32768);
+        else bound = __float_as_uint(f32_unord(top));
+        *reinterpret_cast<uint2 *>(out + 12) = make_uint2(bound, 8u);
+    }
+}
+
 // The first kernel of a solve, one group of G lanes per token:
-//   - the token's score summary: 9 rounds of a group maximum (ties to the
-//     lowest expert) over the lanes' 8 scores each;
+//   - the token's score summary (build_summary, or 9 rounds of a group
+//     maximum, ties to the lowest expert, over the lanes' scores);
 //   - the score range and a non-finite flag over the same loaded scores, one
 //     partial (max, min, bad) per block in rpart[3 * block] (start_kernel
 //     combines them);
@@ -604,6 +710,44 @@ __global__ __launch_bounds__(kThreads) void prologue_kernel(Ctx<M> c0, AssignPar
     for (int t = blockIdx.x * per_block + threadIdx.x / G; t < n_round;
          t += per_block * gridDim.x) {
         const bool valid = t < c.T;
+        if constexpr (G >= 8) {
+            if (c.E <= 8 * G) {
+                uint32_t o[8];
+                const int e0 = 8 * gl;
+                const bool in = valid && e0 < c.E;
+                if (in) load8_ord<M>(c.S, (int64_t)t * c.E, e0, c.E, o);
+                else {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) o[q] = 0x80000000u;
+                }
+                // The range over order-preserving images; non-finite scores
+                // (outside the finite images) only raise the flag.
+                uint32_t mx = 0u, mn = 0xffffffffu;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const bool here = in && e0 + q < c.E;
+                    mx = here && o[q] > mx ? o[q] : mx;
+                    mn = here && o[q] < mn ? o[q] : mn;
+                }
+                if (!M::kInteger && (mx > 0xff7fffffu || mn < 0x00800000u)) {
+                    rbad = 1;
+                    mx = 0u;
+                    mn = 0xffffffffu;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const bool fin = in && e0 + q < c.E && o[q] >= 0x00800000u &&
+                                         o[q] <= 0xff7fffffu;
+                        mx = fin && o[q] > mx ? o[q] : mx;
+                        mn = fin && o[q] < mn ? o[q] : mn;
+                    }
+                }
+                rmx = mx > rmx ? mx : rmx;
+                rmn = mn < rmn ? mn : rmn;
+                if (valid && gl == 0) assign[t] = -1;
+                build_summary<M, G>(c, t, valid, gl, o);
+                continue;
+            }
+        }
         value_t sv[kSumChunks][8];
 #pragma unroll
         for (int ch = 0; ch < kSumChunks; ++ch) {

@@ -2,7 +2,7 @@
 (C up to 256, up to 512, above), experts merged by one wave or by the block,
 more bids for a block's experts than its list holds, one- and two-byte expert
 indices, several experts per block, free slots filled and holders displaced in
-one round."""
+one round. And the score summaries the bids read."""
 import numpy as np
 import pytest
 import torch
@@ -27,7 +27,11 @@ def _scores(T, E, kind, seed):
     S = wl.random_scores(T, E, seed)
     if kind == "crowd":      # every token wants the same expert first
         S[:, E // 2] += 6.0
-    return S
+    if kind == "tied":       # many equal scores, also at the end of a summary
+        S = np.round(S * 4.0) / np.float32(4.0)
+    if kind == "close":      # scores that differ in their last bits only
+        S = (np.float32(1.0) + wl.random_scores(T, E, seed + 1) * np.float32(2e-6))
+    return S.astype(np.float32)
 
 
 @pytest.mark.parametrize("kind", ["normal", "crowd", "int16"])
@@ -51,7 +55,12 @@ def test_same_rounds_as_the_single_workgroup_solver(monkeypatch, T, E, kind):
 
 @pytest.mark.parametrize("T,E,kind", [(16384, 32, "crowd"), (6000, 600, "normal"),
                                       (6000, 600, "crowd"), (12288, 8, "crowd"),
-                                      (4097, 17, "crowd")])
+                                      (4097, 17, "crowd"),
+                                      # the score summaries: rows of part groups and
+                                      # of whole ones, ties at the 8th and 9th score
+                                      (264, 33, "tied"), (512, 64, "tied"), (2000, 100, "close"),
+                                      (2064, 129, "tied"), (4096, 256, "close"),
+                                      (1028, 257, "tied"), (4096, 512, "tied")])
 def test_optimality_bound(T, E, kind):
     """Weak duality at the returned prices certifies the bound, whatever path
     the merges took; every expert is full and perm is the stable sort."""
