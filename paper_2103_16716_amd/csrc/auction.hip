@@ -2069,26 +2069,19 @@ __device__ inline void wave_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Where to look next for the threshold that C keys reach: between lo, which
-// clo > C keys reach, and hi > lo + 1, which chi < C reach (compared in the
-// keys' upper words), by the share of the counts; the middle every third time.
-__device__ inline uint32_t next_trial(uint32_t lo, uint32_t hi, int clo, int chi, int C, int it) {
-    const uint32_t w = hi - lo;
-    const float f = it % 3 == 2 ? 0.5f : (float)(clo - C) / (float)(clo - chi);
-    uint32_t t = lo + (uint32_t)(f * (float)w);
-    t = t <= lo ? lo + 1 : t;
-    return t >= hi ? hi - 1 : t;
-}
-
 // The threshold of a selection over the wave's keys (kk and b; 0 = none,
 // more than C in all): a value that exactly C of them reach. Searched in the
-// keys' upper words by interpolation (five or six counts for a few hundred
-// keys; bit by bit from the top it was over twenty); keys that agree in them
-// are told apart by the lower words, bit by bit.
-constexpr int kLoopFew = 12;
+// keys' upper words, below the leading bits they share, and only as far as
+// needed to part the keys; keys that agree in them are told apart by the
+// lower words. A wave issues an instruction every few cycles, so a step is
+// kept to a compare and a count per key of a lane (interpolating between
+// counts took half the steps of four times the length). With few keys to
+// leave, the next larger upper word, so many times.
+constexpr int kLoopFew = 3;
 template <int NQ>
 __device__ inline uint64_t wave_threshold(const uint64_t (&kk)[NQ], uint64_t b, int C) {
-    uint32_t mn = b != 0 ? (uint32_t)(b >> 32) : ~0u, mx = (uint32_t)(b >> 32);
+    const uint32_t bh = (uint32_t)(b >> 32);
+    uint32_t mn = b != 0 ? bh : ~0u, mx = bh;
     int n = __popcll(__ballot(b != 0));
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -2097,48 +2090,38 @@ __device__ inline uint64_t wave_threshold(const uint64_t (&kk)[NQ], uint64_t b, 
         mx = h > mx ? h : mx;
         n += __popcll(__ballot(kk[q] != 0));
     }
-    uint32_t lo = wave_min_u32(mn);
+    mn = wave_min_u32(mn);
     if (n - C <= kLoopFew) {
-        // Few keys to leave: the next larger upper word, n - C times.
-        int reach = n;
-        for (uint32_t t = lo;;) {
-            int k = __popcll(__ballot((uint32_t)(b >> 32) == t && b != 0));
-            uint32_t nx = (uint32_t)(b >> 32) > t ? (uint32_t)(b >> 32) : ~0u;
+        uint32_t t = mn;
+        for (;;) {
+            int k = __popcll(__ballot(bh == t && b != 0));
+            uint32_t nx = bh > t ? bh : ~0u;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 const uint32_t x = (uint32_t)(kk[q] >> 32);
                 k += __popcll(__ballot(x == t && kk[q] != 0));
                 nx = x > t && x < nx ? x : nx;
             }
-            if (reach - k < C) break;   // (keys that agree: told apart below)
-            reach -= k;
+            if (n - k < C) break;   // (keys that agree: told apart below)
+            n -= k;
             t = wave_min_u32(nx);
-            lo = t;
-            if (reach == C) return (uint64_t)t << 32;
+            if (n == C) return (uint64_t)t << 32;
         }
     }
-    uint32_t hi = ~wave_min_u32(~mx);
-    int clo = n, chi = 0;
-    hi = hi == ~0u ? hi : hi + 1;   // (~0: an overflowed bid, told apart below)
-    for (int it = 0; hi - lo > 1; ++it) {
-        const uint32_t t = next_trial(lo, hi, clo, chi, C, it);
-        int k = __popcll(__ballot((uint32_t)(b >> 32) >= t));
+    mx = ~wave_min_u32(~mx);
+    const int top = mn != mx ? 31 - __clz((int)(mn ^ mx)) : -1;
+    uint32_t t = top >= 31 ? 0u : mn & (~0u << (top + 1));
+    for (int bit = top; bit >= 0; --bit) {
+        const uint32_t trial = t | (1u << bit);
+        int k = __popcll(__ballot(bh >= trial));
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) k += __popcll(__ballot((uint32_t)(kk[q] >> 32) >= t));
+        for (int q = 0; q < NQ; ++q) k += __popcll(__ballot((uint32_t)(kk[q] >> 32) >= trial));
+        t = k >= C ? trial : t;
         if (k == C) return (uint64_t)t << 32;
-        if (k > C) {
-            lo = t;
-            clo = k;
-        } else {
-            hi = t;
-            chi = k;
-        }
     }
-    uint64_t thr = (uint64_t)lo << 32;
-    const bool open = hi == ~0u;   // (the upper words may also be ~0)
-    for (int bit = open ? 32 : 31; bit >= 0; --bit) {
-        const uint64_t trial = thr + (1ull << bit);
-        if (trial < thr) continue;
+    uint64_t thr = (uint64_t)t << 32;
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint64_t trial = thr | (1ull << bit);
         int k = __popcll(__ballot(b >= trial));
 #pragma unroll
         for (int q = 0; q < NQ; ++q) k += __popcll(__ballot(kk[q] >= trial));
@@ -4817,6 +4800,9 @@ constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallT = 2048;
 constexpr int kSmallE = 256;
 constexpr int kSmallRows = 4;   // tokens a bidding group handles per pass (loads first)
+// Bids from which an expert's wave merges them together (about the time of
+// three streamed ones).
+constexpr int kSmallMerge = 4;
 constexpr int kSmallBatch = 8;  // batches from this size take the single-workgroup rounds
 constexpr int kSmallSoloT = 512;   // and single problems up to this many tokens
 
@@ -4891,6 +4877,72 @@ __device__ inline void small_top2(const Ctx<M> &c, const int (&tk)[kSmallRows],
 #pragma unroll
     for (int u = 0; u < kSmallRows; ++u)
         top2_summary<M, G>(c, sw[u], tk[u], ok[u], gl, pr, pmin, v1[u], e1[u], v2[u], s1[u]);
+}
+
+// One wave merges an expert's nb bids (bids, grouped) into its ce held keys h
+// (C <= 64 NQ, in LDS), 64 bids at a time: the C largest stay, kept bids take
+// the free slots, then the slots of the keys that leave (scratch: nb words of
+// the expert's own). Tokens that leave or are refused go to the next active
+// list. Returns the number of held keys.
+template <int NQ>
+__device__ inline int small_merge(uint64_t *h, int ce, int C, const uint64_t *bids,
+                                  uint64_t *scratch, int nb, int T, int *nxt, int *nnext,
+                                  SolveCtrl *ctrl) {
+    const int lane = lane_id();
+    for (int j0 = 0; j0 < nb; j0 += 64) {
+        const int k = nb - j0 < 64 ? nb - j0 : 64;
+        const uint64_t b = lane < k ? bids[j0 + lane] : 0ull;
+        const int room = C - ce;
+        if (k <= room) {
+            if (lane < k) h[ce + lane] = b;
+            ce += k;
+            wave_order();
+            continue;
+        }
+        uint64_t kk[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int s = 64 * q + lane;
+            kk[q] = s < ce ? h[s] : 0ull;
+        }
+        const uint64_t thr = wave_threshold<NQ>(kk, b, C);
+        const bool keep = b != 0 && b >= thr;
+        const uint64_t km = __ballot(keep);
+        const uint64_t rm = __ballot(b != 0 && !keep);
+        int ne = 0;
+        int er[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const bool leave = kk[q] != 0 && kk[q] < thr;
+            const uint64_t lm = __ballot(leave);
+            er[q] = leave ? ne + __popcll(lm & lanemask_lt()) : -1;
+            ne += __popcll(lm);
+            if (leave && er[q] < k) scratch[j0 + er[q]] = (uint64_t)(64 * q + lane);
+        }
+        // The tokens that stay active: the displaced, then the refused.
+        int base = 0;
+        if (lane == 0) base = atomicAdd(nnext, ne + __popcll(rm));
+        base = __builtin_amdgcn_readfirstlane(base);
+        auto leave_at = [&](int at, uint64_t key) {
+            const int t = key_token(key);
+            if (at < T && t >= 0 && t < T) nxt[at] = t;
+            else flag_internal(ctrl);
+        };
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (er[q] >= 0) leave_at(base + er[q], kk[q]);
+        if (b != 0 && !keep) leave_at(base + ne + __popcll(rm & lanemask_lt()), b);
+        wave_order();
+        if (keep) {
+            const int r = __popcll(km & lanemask_lt());
+            const int slot = r < room ? ce + r : (r - room < ne ? (int)scratch[j0 + r - room] : C);
+            if (slot < C) h[slot] = b;
+            else flag_internal(ctrl);
+        }
+        ce = C;
+        wave_order();
+    }
+    return ce;
 }
 
 // One launch runs from the state the control block and the holder tables
@@ -5168,6 +5220,22 @@ __global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, A
             int ce = cnt[e];
             uint64_t mke = mk[e];
             int mse = ms[e];
+            if (nb >= kSmallMerge && C <= 256 && b0 + nb <= T) {
+                if (C <= 64)
+                    ce = small_merge<1>(h, ce, C, bsort + b0, bkey + b0, nb, T, nxt, &s_nnext, ctrl);
+                else
+                    ce = small_merge<4>(h, ce, C, bsort + b0, bkey + b0, nb, T, nxt, &s_nnext, ctrl);
+                mke = ~0ull;
+                mse = 0;
+                for (int q = lane; q < ce; q += 64) {
+                    const uint64_t v = h[q];
+                    if (v < mke) {
+                        mke = v;
+                        mse = q;
+                    }
+                }
+                wave_min_key(mke, mse);
+            } else
             for (int k = 0; k < nb && b0 + k < T; ++k) {
                 const uint64_t b = bsort[b0 + k];
                 int out = -1;

@@ -36,7 +36,7 @@ def _scores(T, E, kind, seed):
 
 @pytest.mark.parametrize("kind", ["normal", "crowd", "int16"])
 @pytest.mark.parametrize("T,E", [(2048, 128), (2048, 8), (2044, 4), (2048, 2), (1000, 250),
-                                 (2047, 23)])
+                                 (2047, 23), (2048, 32), (2015, 31)])
 def test_same_rounds_as_the_single_workgroup_solver(monkeypatch, T, E, kind):
     """The single-workgroup solver runs the same rounds with code of its own:
     assignment, sort vector, prices and round count agree bit for bit. (Without
