@@ -36,6 +36,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -4218,16 +4219,15 @@ constexpr int ssp_block() { return kSspBlock; }
 // small != 0 (tests only) routes every step through the fallbacks: no
 // recompute list (whole rows instead) and received rows read by the owners.
 template <class M, int Ep>
-__global__ __launch_bounds__(ssp_block<Ep>()) void ssp_kernel(Ctx<M> c0, int K, int small) {
+__device__ __attribute__((always_inline)) inline void ssp_run(const Ctx<M> &c, int K, int small,
+                                                              unsigned char *smem_raw) {
     static_assert(!M::kInteger, "the shortest-path finish runs in float mode");
     constexpr int kBlk = ssp_block<Ep>();
     constexpr int kW = kBlk / 64;
     constexpr int RW = Ep / kW;                  // rows per wave
     constexpr int CL = Ep >= 64 ? Ep / 64 : 1;   // columns per lane
     constexpr bool kG = SspLds<Ep>::kGlobal;
-    const Ctx<M> c = c0.at(blockIdx.y);
     SolveCtrl *ctrl = c.ctrl;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     using LY = SspLds<Ep>;
     uint64_t *distp = reinterpret_cast<uint64_t *>(smem_raw + LY::distp);
     uint64_t *rckey = reinterpret_cast<uint64_t *>(smem_raw + LY::rckey);
@@ -4732,6 +4732,98 @@ __global__ __launch_bounds__(ssp_block<Ep>()) void ssp_kernel(Ctx<M> c0, int K, 
     }
 }
 
+template <class M, int Ep>
+__global__ __launch_bounds__(ssp_block<Ep>()) void ssp_kernel(Ctx<M> c0, int K, int small) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const Ctx<M> c = c0.at(blockIdx.y);
+    ssp_run<M, Ep>(c, K, small, smem_raw);
+}
+
+// The exchange matrix as ssp_build_kernel computes it, by one workgroup: a
+// wave per expert, P (the power of two from E on, at most 64) lanes per row and
+// the wave's 64 / P groups splitting the expert's tokens, eight rows in flight.
+template <class M, int Ep>
+__device__ __attribute__((always_inline)) inline void ssp_build_run(const Ctx<M> &c) {
+    constexpr int P = Ep < 64 ? Ep : 64;
+    constexpr int CL = Ep / P;   // columns per lane
+    constexpr int kU = CL > 2 ? 4 : 8;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sub = lane / P, xl = lane % P;
+    constexpr int subs = 64 / P;
+    const int E = c.E, C = c.C;
+    for (int e = wave; e < E; e += (int)(blockDim.x >> 6)) {
+        int cnt = ld_relaxed(&c.hcount[e]);
+        if (cnt < 0 || cnt > C) {
+            if (lane == 0) flag_internal(c.ctrl);
+            cnt = 0;
+        }
+        const uint64_t *hold =
+            c.holders + (int64_t)(ld_relaxed(&c.hsel[e]) & 1) * c.T + (int64_t)e * C;
+        for (int q = lane; q < C; q += 64) {
+            int t = q < cnt ? key_token(hold[q]) : 0;
+            if (t < 0 || t >= c.T) {
+                flag_internal(c.ctrl);
+                t = 0;
+            }
+            c.ssp_t[(int64_t)e * C + q] = (uint16_t)t;
+        }
+        float best[CL];
+        int bs[CL];
+#pragma unroll
+        for (int j = 0; j < CL; ++j) {
+            best[j] = INFINITY;
+            bs[j] = 0xffff;
+        }
+        for (int q0 = sub; q0 < cnt; q0 += subs * kU) {
+            float se[kU], sx[kU][CL];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int q = q0 + u * subs;
+                if (q >= cnt) continue;
+                int t = key_token(hold[q]);
+                if (t < 0 || t >= c.T) t = 0;
+                const float *row = c.S + (int64_t)t * E;
+                se[u] = row[e];
+#pragma unroll
+                for (int j = 0; j < CL; ++j) sx[u][j] = row[xl + P * j < E ? xl + P * j : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int q = q0 + u * subs;
+                if (q >= cnt) continue;
+#pragma unroll
+                for (int j = 0; j < CL; ++j) {
+                    const float v = se[u] - sx[u][j];
+                    const bool t = v < best[j];   // (ascending slots: ties keep the lower)
+                    best[j] = t ? v : best[j];
+                    bs[j] = t ? q : bs[j];
+                }
+            }
+        }
+#pragma unroll
+        for (int off = P; off < 64; off <<= 1) {
+#pragma unroll
+            for (int j = 0; j < CL; ++j) {
+                const float v = __shfl_xor(best[j], off);
+                const int q = __shfl_xor(bs[j], off);
+                const bool t = (v < best[j]) | ((v == best[j]) & (q < bs[j]));
+                best[j] = t ? v : best[j];
+                bs[j] = t ? q : bs[j];
+            }
+        }
+        if (sub == 0) {
+#pragma unroll
+            for (int j = 0; j < CL; ++j) {
+                const int x = xl + P * j;
+                if (x < E) {
+                    c.ssp_m[(int64_t)e * E + x] = best[j];
+                    c.ssp_a[(int64_t)e * E + x] = (uint16_t)bs[j];
+                }
+            }
+        }
+    }
+}
+
 // Wave-wide maximum of (v, i), ties to the lower i; every lane ends with it.
 template <class V>
 __device__ inline V readlane_v(V v, int l) {
@@ -4945,20 +5037,19 @@ __device__ inline int small_merge(uint64_t *h, int ce, int C, const uint64_t *bi
     return ce;
 }
 
-// One launch runs from the state the control block and the holder tables
+// One call runs from the state the control block and the holder tables
 // describe (a phase just begun, a phase the shortest-path finish completed,
 // or one in progress) through as many rounds and phases as it can: it stops
 // when the solve is done, when the round bound is reached, or when at most
 // `cap` tokens of a phase are left (cap > 0: the shortest-path finish takes
-// them; the next launch continues after it), handing the state back in the
+// them; the next call continues after it), handing the state back in the
 // multi-kernel path's layout (holder table 0, active list 0).
 template <class M, int G>
-__global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, AssignParams p,
-                                                                    int cap) {
+__device__ __attribute__((always_inline)) inline void small_rounds(const Ctx<M> &c,
+                                                                   const AssignParams &p, int cap,
+                                                                   unsigned char *smem_raw) {
     using value_t = typename M::value_t;
-    const Ctx<M> c = c0.at(blockIdx.y);
     SolveCtrl *ctrl = c.ctrl;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     const int E = c.E, C = c.C, T = c.T;
     const SmallLds L = small_lds(T, E, (int)sizeof(value_t));
     value_t *pr = reinterpret_cast<value_t *>(smem_raw + L.pr);
@@ -5317,6 +5408,42 @@ __global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, A
         ctrl->active_count[0] = s_n;
         ctrl->active_count[1] = 0;
         ctrl->pad0 = 0;
+    }
+}
+
+// A whole solve in one launch, one workgroup per problem: rounds, the
+// shortest-path finish of a phase's last tokens, and on (nslots calls, the
+// last of them to the end), until the problem is done. Problems of a batch do
+// not wait for each other between the steps, and a step costs no launch:
+// with a launch for each (rounds, exchange matrix, finish, four times over)
+// the solve of T = 512, E = 8 took 154 us, 134 this way, and 256 shuffled
+// problems of T = 2048, E = 128 with their rows routed 3600, 3455 this way.
+template <class M, int G>
+__global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, AssignParams p,
+                                                                    int ssp_cap, int nslots,
+                                                                    int fallbacks) {
+    constexpr int Ep = 8 * G > 256 ? 256 : (8 * G < 32 ? 32 : 8 * G);   // E <= kSmallE = 256
+    const Ctx<M> c = c0.at(blockIdx.y);
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int s_done;
+    for (int slot = 0; slot < nslots; ++slot) {
+        const int cap = slot < nslots - 1 ? ssp_cap : 0;
+        small_rounds<M, G>(c, p, cap, smem_raw);
+        __syncthreads();
+        if (threadIdx.x == 0) s_done = c.ctrl->done || c.ctrl->internal_error;
+        __syncthreads();
+        if (s_done) return;
+        if constexpr (!M::kInteger) {
+            if (cap > 0) {
+                int n = 0;
+                if (ssp_pending<M>(c, &n)) {   // (uniform: every thread reads the same words)
+                    ssp_build_run<M, Ep>(c);
+                    __syncthreads();
+                    ssp_run<M, Ep>(c, c.ssp_cap, fallbacks, smem_raw);
+                    __syncthreads();
+                }
+            }
+        }
     }
 }
 
@@ -6198,9 +6325,10 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     const bool small = small_fits && (small_set == 1 ||
                                       (small_set < 0 && (B >= kSmallBatch || c.T <= kSmallSoloT)));
     if (small) {
-        const size_t bytes = small_lds(c.T, c.E, (int)sizeof(value_t)).total;
+        const size_t bytes =
+            std::max(small_lds(c.T, c.E, (int)sizeof(value_t)).total, ssp_r > 0 ? ssp_bytes : 0);
         const void *fn = reinterpret_cast<const void *>(&small_solve_kernel<M, G>);
-        const hipError_t err = bytes + 1024 <= (size_t)facts.optin ? lds_optin(dev, fn, bytes)
+        const hipError_t err = bytes + 2048 <= (size_t)facts.optin ? lds_optin(dev, fn, bytes)
                                                                      : hipErrorInvalidValue;
         if (err == hipSuccess) {
             int nslots = (p.flags & BASE_ASSIGN_FULL_SCHEDULE) ? 6 : 5;
@@ -6212,25 +6340,14 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
                     ++nslots;
                 }
             }
-            if (ssp_r == 0) nslots = 1;   // nothing hands over between launches
-            for (int slot = 0; slot < nslots; ++slot) {
-                const bool last = slot == nslots - 1;
-                const int cap = (!last && ssp_r > 0) ? c.ssp_cap : 0;
-                // (the dominant kernel of this route, timed like the engine)
-                hipEvent_t ev0 = nullptr, ev1 = nullptr;
-                timing_pair(&ev0, &ev1);
-                if (ev0 != nullptr) (void)hipEventRecord(ev0, s);
-                hipLaunchKernelGGL((small_solve_kernel<M, G>), dim3(1, B), dim3(kSmallThreads),
-                                   bytes, s, c, p, cap);
-                if (ev1 != nullptr) (void)hipEventRecord(ev1, s);
-                if constexpr (!M::kInteger) {
-                    if (cap > 0) {
-                        hipLaunchKernelGGL(ssp_build_kernel<M>, dim3(c.E, B),
-                                           dim3(ssp_build_threads(c.C, c.E * B)), 0, s, c);
-                        launch_ssp<M>(c, B, ssp_r, ssp_bytes, s);
-                    }
-                }
-            }
+            // (the dominant kernel of this route, timed like the engine)
+            hipEvent_t ev0 = nullptr, ev1 = nullptr;
+            timing_pair(&ev0, &ev1);
+            if (ev0 != nullptr) (void)hipEventRecord(ev0, s);
+            hipLaunchKernelGGL((small_solve_kernel<M, G>), dim3(1, B), dim3(kSmallThreads), bytes,
+                               s, c, p, ssp_r > 0 ? c.ssp_cap : 0, nslots,
+                               ssp_fallbacks_setting());
+            if (ev1 != nullptr) (void)hipEventRecord(ev1, s);
             return hipGetLastError();
         }
         (void)hipGetLastError();
