@@ -278,12 +278,16 @@ __device__ inline int ld_relaxed(const int *p) {
 
 // Copies n16 16-byte words from global memory to LDS with kBlock threads,
 // eight loads in flight per thread before any store (a plain loop waits for
-// each load before the next).
+// each load before the next). A vector type: an array of uint4 structures
+// filled under a condition goes through scratch memory.
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 template <int kBlock>
-__device__ inline void copy16_to_lds(uint4 *dst, const uint4 *src, int n16) {
+__device__ inline void copy16_to_lds(uint4 *dst4, const uint4 *src4, int n16) {
     constexpr int kU = 8;
+    u32x4_t *dst = reinterpret_cast<u32x4_t *>(dst4);
+    const u32x4_t *src = reinterpret_cast<const u32x4_t *>(src4);
     for (int i0 = threadIdx.x; i0 < n16; i0 += kU * kBlock) {
-        uint4 v[kU];
+        u32x4_t v[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int i = i0 + u * kBlock;
@@ -4400,6 +4404,13 @@ __device__ __attribute__((always_inline)) inline void ssp_run(const Ctx<M> &c, i
         float D = INFINITY;
         int f = 0x7fffffff;   // the nearest expert with room
         for (int it = 0;; ++it) {
+            // (The arcs' M(e,x) + p_x are not to be hoisted out of the search:
+            // they need as many registers again, and spilling M made an
+            // augmentation at E = 256 take 40 us, four times that at E = 128.)
+            if constexpr (kG) {
+#pragma unroll
+                for (int j = 0; j < CL; ++j) asm volatile("" : "+v"(pxl[j]));
+            }
             const uint64_t *cur = distp + (it % 3) * Ep;
             uint64_t *nxt = distp + ((it + 1) % 3) * Ep;
             if (tid < Ep) {
