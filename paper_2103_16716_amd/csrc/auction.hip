@@ -175,6 +175,7 @@ struct Ctx {
     int *ovf_exp, *active;
     int *ovf_count;   // lives in ctrl->pad0
     int engine_cap;   // > 0: rounds with at most this many active tokens go to the engine
+    int early_from;   // a phase ends early only after a round of more active tokens than this
     int eng_k;        // length of the engine's per-expert lists of lowest keys
     uint64_t *eng_ck; // the lists as built at the engine's entry
     uint16_t *eng_cs;
@@ -250,6 +251,7 @@ Ctx<M> make_ctx(const void *S, const AssignParams &p, char *ws) {
     c.active = reinterpret_cast<int *>(ws + L.active);
     c.ovf_count = &c.ctrl->pad0;
     c.engine_cap = 0;
+    c.early_from = 0;
     c.eng_k = 8;
     c.eng_ck = reinterpret_cast<uint64_t *>(ws + L.eck);
     c.eng_cs = reinterpret_cast<uint16_t *>(ws + L.ecs);
@@ -2571,7 +2573,8 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         const int n = all ? c.T : ctrl->active_count[cur];
         st_rounds = ctrl->rounds;
         st_go = !ctrl->done && !ctrl->internal_error && n > 0 && n <= c.T &&
-                (all || n > c.engine_cap) && (free_rounds > 0 || st_rounds < max_rounds);
+                (all || n > c.engine_cap) &&
+                ((free_rounds > 0 && (all || n > c.early_from)) || st_rounds < max_rounds);
         st_cur = cur;
         st_all = all;
         st_n = n;
@@ -2887,6 +2890,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         // (4) The round is closed (see end_round); this block's tokens for the next.
         bids += (unsigned long long)n;
         ++rounds;
+        const int n_before = n;
         n = s_sum;
         const int m_old = m;
         for (int j0 = 0; j0 < m_old; j0 += kLoopThreads) {
@@ -2909,10 +2913,10 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         }
         __syncthreads();
         m = s_pack;
-        early = n > 0 && c.early_n != 0 && !last_phase &&
+        early = n > 0 && n_before > c.early_from && c.early_n != 0 && !last_phase &&
                 n <= (c.early_n > 0 ? c.early_n : -c.early_n) && (c.early_n < 0 || early_ok);
         if (n == 0 || early || n <= c.engine_cap || rounds >= max_wide ||
-            (rounds >= free_rounds && st_rounds + rounds >= max_rounds))
+            (st_rounds + rounds >= max_rounds && !(rounds < free_rounds && n > c.early_from)))
             break;
         __syncthreads();
     }
@@ -3052,7 +3056,8 @@ __device__ inline void lds_barrier() {
 
 constexpr int kEngThreads = 1024;
 constexpr int kEngWaves = kEngThreads / 64;
-constexpr int kEngCap = 256;
+constexpr int kEngCap = 256;     // most active tokens it can take
+constexpr int kEngTake = 128;    // those it takes over from a single problem's round loop
 constexpr int kEngDirect = 64;   // rounds with at most this many bids skip the grouping
 constexpr int kEngMaxE = 512;
 constexpr int kEngMaxC = 512;    // holder tables a wave holds in registers (8 keys per lane)
@@ -3772,7 +3777,7 @@ __global__ __launch_bounds__(kEngThreads) void engine_kernel(Ctx<M> c0, AssignPa
         if (!ctrl->done && !ctrl->all_active) {
             s_cur = ctrl->cur;
             const int n = ld_relaxed(&ctrl->active_count[s_cur]);
-            if (n > 0 && n > c.ssp_cap && n <= kEngCap) {
+            if (n > 0 && n > c.ssp_cap && n <= c.engine_cap) {
                 s_go = 1;
                 s_n = n;
             }
@@ -6275,7 +6280,7 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
             c.eng_k = K;
         }
     }
-    if (engine) c.engine_cap = kEngCap;
+    if (engine) c.engine_cap = c.early_from = kEngCap;
     {
         // Early ends of large-epsilon phases; with the full schedule no
         // check reads any phase above the last, so each of them may end
@@ -6424,6 +6429,12 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
             }
         }
     }
+    // A round of the loop costs a single problem about 10 us whatever the few
+    // hundred bids; one of the engine grows with them. The engine taking over
+    // at 256, 128, 96, 64 and 32: T = 65536, E = 256 2814, 2725, 2709, 2715,
+    // 2906 us; T = 32768, E = 128 (clustered) 921, 909, 912, 927, 994; T = 2048,
+    // E = 128 714, 707, 707, 712, 748; T = 8192, E = 64 603, 605, 612, 620, 659.
+    if (engine && coop_blocks > 0 && B == 1) c.engine_cap = kEngTake;
     // Each slot: the phase start (with the decision on the previous slot's
     // duality check), the wide rounds, the round loop, the engine, the
     // one-workgroup tail (with the engine only in the last slot: a phase the
