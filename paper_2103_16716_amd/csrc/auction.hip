@@ -3193,9 +3193,8 @@ __device__ inline int lds_rank(const uint64_t *keys, int n, uint64_t key) {
 
 // The K lowest keys of the expert's holder table, sorted, into the lanes.
 // The table is read from global memory and patched with the pending stores;
-// the K-th smallest key is found by a bitwise search on ballot counts, the
-// keys up to it are compacted through the wave's LDS scratch, and a 64-lane
-// bitonic network sorts them.
+// the threshold above the K smallest keys comes from wave_threshold, the keys
+// below it are compacted through the wave's LDS scratch and placed by rank.
 template <class M>
 __device__ void er_refill(const Ctx<M> &c, const uint64_t *hold, int K, ExpertRegs<M> &r,
                           uint64_t *scr_key, int *scr_slot) {
@@ -3204,7 +3203,7 @@ __device__ void er_refill(const Ctx<M> &c, const uint64_t *hold, int K, ExpertRe
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int idx = lane + 64 * q;
-        kk[q] = idx < r.cnt ? hold[idx] : ~0ull;
+        kk[q] = idx < r.cnt ? hold[idx] : 0ull;
     }
     for (int j = 0; j < r.np; ++j) {
         const int slot = rl32(r.pslot, j);
@@ -3220,82 +3219,12 @@ __device__ void er_refill(const Ctx<M> &c, const uint64_t *hold, int K, ExpertRe
     r.key = ~0ull;
     r.slot = 0;
     if (take == 0) return;
-    // thr: the largest value with fewer than `take` keys below it, i.e. the
-    // take-th smallest key (keys are distinct). The bits above the highest
-    // one where the smallest and largest key differ are common to every key
-    // (and to thr): the search starts below them.
-    uint64_t kmin = ~0ull, kmax = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        if (kk[q] != ~0ull) {
-            kmin = kk[q] < kmin ? kk[q] : kmin;
-            kmax = kk[q] > kmax ? kk[q] : kmax;
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint64_t a = __shfl_xor(kmin, off), b = __shfl_xor(kmax, off);
-        kmin = a < kmin ? a : kmin;
-        kmax = b > kmax ? b : kmax;
-    }
-    const uint64_t kdiff = kmin ^ kmax;
-    const int top = kdiff ? 63 - __clzll((long long)kdiff) : 0;
-    uint64_t thr = top >= 63 ? 0ull : kmin & (~0ull << (top + 1));
-    // Bit by bit over the top 12 differing bits; then, when at most 64 keys
-    // share the prefix found, the take-th smallest is among them (the keys
-    // below the prefix are fewer than take, those up to its end at least
-    // take): ranking them finishes the search. Otherwise the bits go on.
-    const int lo = top >= 12 ? top - 11 : 0;
-    int bit = top;
-    for (; bit >= lo; --bit) {
-        const uint64_t trial = thr | (1ull << bit);
-        int below = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) below += __popcll(__ballot(kk[q] < trial));
-        if (below < take) thr = trial;
-    }
-    if (lo > 0) {
-        const uint64_t hi = thr >> lo;
-        int below = 0, inb = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            below += __popcll(__ballot((kk[q] >> lo) < hi));
-            inb += __popcll(__ballot((kk[q] >> lo) == hi));
-        }
-        if (inb <= 64) {
-            int at = 0;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const bool in = (kk[q] >> lo) == hi;
-                const uint64_t m = __ballot(in);
-                if (in) scr_key[at + __popcll(m & lanemask_lt())] = kk[q];
-                at += __popcll(m);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint64_t bk = lane < inb ? scr_key[lane] : ~0ull;
-            const int need = take - below;   // in [1, inb]
-            const uint64_t hit = __ballot(lane < inb && lds_rank(scr_key, inb, bk) == need - 1);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (hit != 0) thr = rl64(bk, __ffsll((long long)hit) - 1);
-            else flag_internal(c.ctrl);
-            bit = -1;
-        }
-    }
-    for (; bit >= 0; --bit) {
-        const uint64_t trial = thr | (1ull << bit);
-        int below = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) below += __popcll(__ballot(kk[q] < trial));
-        if (below < take) thr = trial;
-    }
+    // The keys below thr: all but the largest cnt - take.
+    const uint64_t thr = take < r.cnt ? wave_threshold<8>(kk, 0ull, r.cnt - take) : ~0ull;
     int base = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        const bool sel = kk[q] <= thr;
+        const bool sel = kk[q] != 0 && kk[q] < thr;
         const uint64_t m = __ballot(sel);
         if (sel) {
             const int at = base + __popcll(m & lanemask_lt());
