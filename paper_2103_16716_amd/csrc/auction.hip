@@ -272,6 +272,15 @@ Ctx<M> make_ctx(const void *S, const AssignParams &p, char *ws) {
 
 __device__ inline int lane_id() { return threadIdx.x & 63; }
 
+// The thread's index as a value the compiler knows nothing about: parts of a
+// kernel that run in turn inside a loop use one each, so that their addresses
+// are formed where they are used and not kept in registers across the others.
+__device__ inline int opaque_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // Counters that other waves update with atomics are read with atomic loads so
 // that no stale cached copy is used.
 __device__ inline int ld_relaxed(const int *p) {
@@ -2564,9 +2573,6 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         s_und;
     SolveCtrl *ctrl = c.ctrl;
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    uint64_t *scr = reinterpret_cast<uint64_t *>(smem_raw + L.scr) + wave * 2 * 64;
     if (tid == 0) {
         const int cur = ctrl->cur & 1;
         const int all = ctrl->all_active;
@@ -2623,13 +2629,18 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         hc[i] = h;
         hs[i] = sl & 1;
     }
-    const int gl = lane & (G - 1);
     int n = st_n;
     int rounds = 0;
     uint32_t seq = 0;
     unsigned long long bids = 0;
     bool early = false;
     for (;;) {
+        // (a new index per round: see opaque_tid)
+        const int tid = opaque_tid();
+        const int lane = tid & 63;
+        const int wave = tid >> 6;
+        const int gl = lane & (G - 1);
+        uint64_t *scr = reinterpret_cast<uint64_t *>(smem_raw + L.scr) + wave * 2 * 64;
         // (1) This block's bids against the prices at the start of the round.
         for (int e = tid; e < c.E; e += kLoopThreads) pr[e] = ld_price(c.prices + e);
         for (int i = tid; i < owned; i += kLoopThreads) lec[i] = 0;
@@ -2929,6 +2940,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         ++seq;
         if (!loop_barrier(c.flags, seq, nb, (uint32_t)m, cnt, ctrl, poll_limit)) return;
         if (tid < 64) {
+            const int lane = tid;
             int before = 0;
             if (lane < blk) before += cnt[lane];
             if (lane + 64 < blk) before += cnt[lane + 64];
@@ -4189,7 +4201,7 @@ __device__ __attribute__((always_inline)) inline void ssp_run(const Ctx<M> &c, i
     // it instead of each reducing the labels of every expert.
     __shared__ uint64_t s_rkey[3];
 
-    const int tid = threadIdx.x;
+    const int tid = opaque_tid();
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int E = c.E, C = c.C, T = c.T;
@@ -4692,7 +4704,8 @@ __device__ __attribute__((always_inline)) inline void ssp_build_run(const Ctx<M>
     constexpr int P = Ep < 64 ? Ep : 64;
     constexpr int CL = Ep / P;   // columns per lane
     constexpr int kU = CL > 2 ? 4 : 8;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tid = opaque_tid();
+    const int lane = tid & 63, wave = tid >> 6;
     const int sub = lane / P, xl = lane % P;
     constexpr int subs = 64 / P;
     const int E = c.E, C = c.C;
@@ -5014,7 +5027,7 @@ __device__ __attribute__((always_inline)) inline void small_rounds(const Ctx<M> 
     __shared__ int s_n, s_nnext, s_ntch, s_stop, s_last;
     __shared__ value_t s_eps, s_early_eps;
     __shared__ double s_part[kSmallWaves], s_pmax[kSmallWaves];
-    const int tid = threadIdx.x;
+    const int tid = opaque_tid();
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int per = kSmallThreads / G;
