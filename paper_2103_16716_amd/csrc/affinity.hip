@@ -13,7 +13,7 @@
 //   affinity_pipe_kernel   BM tokens x BN experts per block; chunks of 128
 //                          bytes of a row of both operands go straight from
 //                          global memory into a ring of LDS stages
-//   affinity_small_kernel  32 x 32 outputs per block, whose waves split d:
+//   affinity_small_kernel  32 x 32 or 32 x 64 outputs per block, whose waves split d:
 //                          problems with too few outputs to give every
 //                          compute unit a tile of the pipelined kernel
 //
@@ -250,54 +250,60 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
 
 // ---------------------------------------------------------- small problems --
 //
-// A block owns 32 tokens x 32 experts (2 x 2 tiles of 16 x 16) and its
+// A block owns 32 tokens x 16 NJ experts (2 x NJ tiles of 16 x 16) and its
 // kSWaves waves split d: wave w takes a contiguous run of the 64-byte steps
 // of a row, loading its matrix operands straight from memory (a load
 // instruction covers 16 rows x 64 bytes; two register sets of kSU steps in
 // flight). The waves' partial tiles are added in LDS in wave order (a fixed
-// order: the result does not depend on scheduling), one tile per wave.
+// order: the result does not depend on scheduling), NJ / 2 tiles per wave.
+// Bound by what a compute unit draws from the L2 (about 20 bytes a clock), so
+// 64 experts a block where there are blocks enough: fp32, 8192 x 64 x 1024,
+// 17.6 us against 21.5 at 32 experts.
 constexpr int kST = 32;
 constexpr int kSWaves = 4;
-constexpr int kSU = 4;   // steps per register set (two sets in flight)
 
-template <class In>
+template <class In, int NJ>
 __global__ __launch_bounds__(64 * kSWaves) void affinity_small_kernel(
     const typename In::elem_t *__restrict__ H, const int32_t *__restrict__ rows, int64_t h_rows,
     const typename In::elem_t *__restrict__ W, float *__restrict__ S, int T, int E, int d) {
     using unit_t = typename In::unit_t;
     constexpr int kStep = 4 * In::kPer;   // elements of a row per step
-    __shared__ f32x4_t red[kSWaves][4][64];
+    constexpr int kSU = NJ == 2 ? 4 : 2;  // steps per register set
+    __shared__ f32x4_t red[kSWaves][2 * NJ][64];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int lrow = lane & 15;
     const int lq = lane >> 4;
     int mt, nt;
-    tile_of(blockIdx.x, (E + kST - 1) / kST, mt, nt);
+    tile_of(blockIdx.x, (E + 16 * NJ - 1) / (16 * NJ), mt, nt);
     if ((int64_t)mt * kST >= T) return;
     const int m0 = mt * kST;
-    const int n0 = nt * kST;
+    const int n0 = nt * 16 * NJ;
     // Operand rows: tokens m0 + 16 x + lane % 16, experts n0 + 16 j + lane %
     // 16; lane / 16 picks the unit of the step.
     const int steps = (d + kStep - 1) / kStep;
     const int q = (steps + kSWaves - 1) / kSWaves;   // steps per wave
     const int s0 = wave * q;
     const int s1 = s0 + q < steps ? s0 + q : steps;
-    const typename In::elem_t *pa[2], *pb[2];
+    const typename In::elem_t *pa[2], *pb[NJ];
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         const int t = m0 + 16 * x + lrow;
         int64_t hr = t < T ? source_row(rows, h_rows, t) : 0;
         if (hr < 0) hr = 0;
-        const int e = n0 + 16 * x + lrow;
         pa[x] = H + hr * d + lq * In::kPer;
-        pb[x] = W + (int64_t)(e < E ? e : E - 1) * d + lq * In::kPer;
     }
-    f32x4_t acc[2][2];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int e = n0 + 16 * j + lrow;
+        pb[j] = W + (int64_t)(e < E ? e : E - 1) * d + lq * In::kPer;
+    }
+    f32x4_t acc[2][NJ];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[x][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    unit_t a[2][kSU][2], b[2][kSU][2];
+        for (int j = 0; j < NJ; ++j) acc[x][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    unit_t a[2][kSU][2], b[2][kSU][NJ];
     auto load = [&](int set, int s) {
 #pragma unroll
         for (int u = 0; u < kSU; ++u) {
@@ -306,12 +312,13 @@ __global__ __launch_bounds__(64 * kSWaves) void affinity_small_kernel(
                 // (units past d, in the last step only, are zero)
                 const bool in = k + lq * In::kPer < d;
 #pragma unroll
-                for (int x = 0; x < 2; ++x) {
+                for (int x = 0; x < 2; ++x)
                     a[set][u][x] = *reinterpret_cast<const unit_t *>(
                         in ? (const void *)(pa[x] + k) : (const void *)&zero_unit);
-                    b[set][u][x] = *reinterpret_cast<const unit_t *>(
-                        in ? (const void *)(pb[x] + k) : (const void *)&zero_unit);
-                }
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    b[set][u][j] = *reinterpret_cast<const unit_t *>(
+                        in ? (const void *)(pb[j] + k) : (const void *)&zero_unit);
             }
         }
     };
@@ -324,7 +331,7 @@ __global__ __launch_bounds__(64 * kSWaves) void affinity_small_kernel(
 #pragma unroll
                     for (int x = 0; x < 2; ++x)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
+                        for (int j = 0; j < NJ; ++j)
                             acc[x][j] = In::mma16(a[set][u][x], b[set][u][j], acc[x][j], i);
             }
     };
@@ -338,20 +345,24 @@ __global__ __launch_bounds__(64 * kSWaves) void affinity_small_kernel(
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) red[wave][2 * x + j][lane] = acc[x][j];
+        for (int j = 0; j < NJ; ++j) red[wave][NJ * x + j][lane] = acc[x][j];
     __syncthreads();
-    static_assert(kSWaves == 4, "one tile per wave below");
-    f32x4_t sum = red[0][wave][lane];
+    static_assert(kSWaves == 4, "NJ / 2 tiles per wave below");
 #pragma unroll
-    for (int w = 1; w < kSWaves; ++w) sum += red[w][wave][lane];
-    // 16x16 accumulator layout: lane holds column lane % 16; register i holds
-    // row 4 (lane / 16) + i.
-    const int e = n0 + 16 * (wave & 1) + lrow;
-    if (e >= E) return;
+    for (int r = 0; r < NJ / 2; ++r) {
+        const int tile = wave * (NJ / 2) + r;
+        f32x4_t sum = red[0][tile][lane];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = m0 + 16 * (wave >> 1) + 4 * lq + i;
-        if (t < T) S[(int64_t)t * E + e] = source_row(rows, h_rows, t) >= 0 ? sum[i] : 0.0f;
+        for (int w = 1; w < kSWaves; ++w) sum += red[w][tile][lane];
+        // 16x16 accumulator layout: lane holds column lane % 16; register i
+        // holds row 4 (lane / 16) + i.
+        const int e = n0 + 16 * (tile % NJ) + lrow;
+        if (e >= E) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = m0 + 16 * (tile / NJ) + 4 * lq + i;
+            if (t < T) S[(int64_t)t * E + e] = source_row(rows, h_rows, t) >= 0 ? sum[i] : 0.0f;
+        }
     }
 }
 
@@ -396,9 +407,10 @@ hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_
 //   128 x 128  1.05 (32768 x 128 x 2048: 33 us, 256 x 128 tiles 41)
 //   128 x 64   0.66 (16384 x 128 x 2048: 21 us, 128 x 128 tiles 27)
 //   64 x 64    0.46 (8192 x 128 x 2048: 17 us, 128 x 64 tiles 20)
+//   32 x 64    0.42 (4096 x 128 x 2048: 14 us, 64 x 64 tiles 16, 32 x 32 17.5)
 //   32 x 32    0.30 (2048 x 128 x 2048: 10 us, 64 x 64 tiles 16)
 // fp32 is bound by the matrix cores at the larger tiles (32 elements a chunk;
-// 65536 x 256 x 2048: 531 us, 130 TFLOP/s; 8192 x 64 x 1024: 23 us against 64
+// 65536 x 256 x 2048: 531 us, 130 TFLOP/s; 8192 x 64 x 1024: 17.6 us against 64
 // on the vector units). Its 256 x 256 and 128 x 128 tiles are never the
 // faster ones and not built.
 struct TileCost {
@@ -407,7 +419,7 @@ struct TileCost {
 };
 constexpr TileCost kTiles[] = {{256, 256, 2.4, 1e30}, {256, 128, 1.55, 4.1}, {256, 64, 1.07, 2.27},
                                {128, 128, 1.05, 1e30}, {128, 64, 0.66, 1.25}, {64, 64, 0.46, 0.75},
-                               {kST, kST, 0.30, 0.32}};
+                               {kST, 64, 0.42, 0.44}, {kST, 32, 0.30, 0.32}};
 constexpr int64_t kComputeUnits = 256;
 
 template <class In>
@@ -428,6 +440,17 @@ int pick_tile(int64_t T, int64_t E) {
     return best;
 }
 
+template <class In, int NJ>
+hipError_t launch_small(const typename In::elem_t *H, const int32_t *rows, int64_t h_rows,
+                        const typename In::elem_t *W, float *S, int64_t T, int64_t E, int64_t d,
+                        hipStream_t stream) {
+    const int64_t nm8 = ((T + kST - 1) / kST + 7) / 8 * 8;
+    const int64_t nn = (E + 16 * NJ - 1) / (16 * NJ);
+    hipLaunchKernelGGL((affinity_small_kernel<In, NJ>), dim3((unsigned)(nm8 * nn)),
+                       dim3(64 * kSWaves), 0, stream, H, rows, h_rows, W, S, (int)T, (int)E, (int)d);
+    return hipGetLastError();
+}
+
 template <class In>
 hipError_t launch_affinity(const typename In::elem_t *H, const int32_t *rows, int64_t h_rows,
                            const typename In::elem_t *W, float *S, int64_t T, int64_t E, int64_t d,
@@ -446,13 +469,10 @@ hipError_t launch_affinity(const typename In::elem_t *H, const int32_t *rows, in
             break;
         case 4: return launch_pipe<In, 128, 64, 1, 1, 4>(H, rows, h_rows, W, S, T, E, d, stream);
         case 5: return launch_pipe<In, 64, 64, 1, 1, 4>(H, rows, h_rows, W, S, T, E, d, stream);
+        case 6: return launch_small<In, 4>(H, rows, h_rows, W, S, T, E, d, stream);
         default: break;
     }
-    const int64_t nm8 = ((T + kST - 1) / kST + 7) / 8 * 8;
-    const int64_t nn = (E + kST - 1) / kST;
-    hipLaunchKernelGGL(affinity_small_kernel<In>, dim3((unsigned)(nm8 * nn)), dim3(64 * kSWaves),
-                       0, stream, H, rows, h_rows, W, S, (int)T, (int)E, (int)d);
-    return hipGetLastError();
+    return launch_small<In, 2>(H, rows, h_rows, W, S, T, E, d, stream);
 }
 
 }  // namespace

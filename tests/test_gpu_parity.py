@@ -114,14 +114,15 @@ def test_affinity_workloads(name):
 
 
 # Shapes for which the tile rule takes each of its tiles (bf16: 256 x 256, 256 x
-# 128, 256 x 64, 128 x 128, 128 x 64, 64 x 64, 32 x 32; fp32: 256 x 128, 256 x
-# 64, 128 x 64, 64 x 64, 32 x 32), one past a whole number of tiles in T, not
+# 128, 256 x 64, 128 x 128, 128 x 64, 64 x 64, 32 x 64, 32 x 32; fp32: 256 x 128, 256 x
+# 64, 128 x 64, 64 x 64, 32 x 64, 32 x 32), one past a whole number of tiles in T, not
 # a multiple in E; d below, at and past a chunk, and with a part chunk.
 @pytest.mark.parametrize("dtype,T,E,d", [
     ("bf16", 32769, 200, 72), ("bf16", 16385, 200, 128), ("bf16", 32769, 50, 136),
     ("bf16", 16385, 100, 264), ("bf16", 16385, 60, 56), ("bf16", 8193, 60, 520),
-    ("bf16", 1025, 60, 1000), ("f32", 65025, 120, 40), ("f32", 65025, 50, 32),
-    ("f32", 16385, 60, 72), ("f32", 8193, 120, 24), ("f32", 1025, 60, 1000)])
+    ("bf16", 7169, 60, 264), ("bf16", 1025, 60, 1000), ("f32", 65025, 120, 40), ("f32", 65025, 50, 32),
+    ("f32", 16385, 60, 72), ("f32", 8193, 120, 24), ("f32", 4161, 120, 72), ("f32", 4033, 120, 72),
+    ("f32", 1025, 60, 1000)])
 def test_affinity_every_tile(dtype, T, E, d):
     rng = np.random.Generator(np.random.PCG64(T + 7 * E + d))
     H = rng.standard_normal((T, d), dtype=np.float32)
