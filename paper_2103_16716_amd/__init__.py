@@ -139,25 +139,38 @@ def _check(status: int, where: str) -> None:
         raise BaseError(status, where)
 
 
+# torch and what the calls below ask it on every call, looked up once (a small
+# call's time is the host's).
+_torch_mod = None
+_codes = {}
+_raw_stream = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod, _raw_stream
+    if _torch_mod is None:
+        import torch
+        _codes.update({torch.bfloat16: BASE_BF16, torch.float32: BASE_F32,
+                       torch.int16: BASE_I16})
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch_mod = torch
+    return _torch_mod
 
 
 def _dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.bfloat16:
-        return BASE_BF16
-    if t.dtype == torch.float32:
-        return BASE_F32
-    if t.dtype == torch.int16:
-        return BASE_I16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    _torch()
+    code = _codes.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _stream_ptr(stream) -> int:
     torch = _torch()
     if stream is None:
+        # the current device's current stream, without a Stream object around it
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
