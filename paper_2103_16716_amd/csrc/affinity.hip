@@ -409,6 +409,10 @@ hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_
 //   64 x 64    0.46 (8192 x 128 x 2048: 17 us, 128 x 64 tiles 20)
 //   32 x 64    0.42 (4096 x 128 x 2048: 14 us, 64 x 64 tiles 16, 32 x 32 17.5)
 //   32 x 32    0.30 (2048 x 128 x 2048: 10 us, 64 x 64 tiles 16)
+// Blocks of the small kernel share a compute unit, so turns after the first
+// cost it a fifth less (bf16; 8192 x 128 x 2048 in 32 x 32: 31 us). Rows that
+// are not whole 128-byte lines make the pipelined chunks span two (40379 x 26 x
+// 232 in bf16: 256 x 64 tiles 9.9 us, 32 x 32 7.1).
 // fp32 is bound by the matrix cores at the larger tiles (32 elements a chunk;
 // 65536 x 256 x 2048: 531 us, 130 TFLOP/s; 8192 x 64 x 1024: 17.6 us against 64
 // on the vector units). Its 256 x 256 and 128 x 128 tiles are never the
@@ -423,15 +427,21 @@ constexpr TileCost kTiles[] = {{256, 256, 2.4, 1e30}, {256, 128, 1.55, 4.1}, {25
 constexpr int64_t kComputeUnits = 256;
 
 template <class In>
-int pick_tile(int64_t T, int64_t E) {
+int pick_tile(int64_t T, int64_t E, int64_t d) {
     constexpr bool kBf16 = In::kPer == 8;
+    const bool whole = d * (int64_t)sizeof(typename In::elem_t) % kChunk == 0;
     int best = 0;
     double low = 0.0;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const TileCost &t = kTiles[i];
         const int64_t tiles = ((T + t.bm - 1) / t.bm) * ((E + t.bn - 1) / t.bn);
-        const double cost = (double)((tiles + kComputeUnits - 1) / kComputeUnits) *
-                            (kBf16 ? t.bf16 : t.f32);
+        const double turns = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
+        double cost = turns * (kBf16 ? t.bf16 : t.f32);
+        if (t.bm > kST) {
+            if (!whole) cost *= 1.4;
+        } else if (kBf16) {
+            cost *= 0.8 + 0.2 / turns;
+        }
         if (i == 0 || cost < low) {
             best = i;
             low = cost;
@@ -456,7 +466,7 @@ hipError_t launch_affinity(const typename In::elem_t *H, const int32_t *rows, in
                            const typename In::elem_t *W, float *S, int64_t T, int64_t E, int64_t d,
                            hipStream_t stream) {
     constexpr bool kBf16 = In::kPer == 8;
-    switch (pick_tile<In>(T, E)) {
+    switch (pick_tile<In>(T, E, d)) {
         case 0:
             if constexpr (kBf16)
                 return launch_pipe<In, 256, 256, 2, 4, 2>(H, rows, h_rows, W, S, T, E, d, stream);

@@ -121,7 +121,7 @@ def test_affinity_workloads(name):
     ("bf16", 32769, 200, 72), ("bf16", 16385, 200, 128), ("bf16", 32769, 50, 136),
     ("bf16", 16385, 100, 264), ("bf16", 16385, 60, 56), ("bf16", 8193, 60, 520),
     ("bf16", 7169, 60, 264), ("bf16", 1025, 60, 1000), ("f32", 65025, 120, 40), ("f32", 65025, 50, 32),
-    ("f32", 16385, 60, 72), ("f32", 8193, 120, 24), ("f32", 4161, 120, 72), ("f32", 4033, 120, 72),
+    ("f32", 16385, 60, 64), ("f32", 8193, 60, 32), ("f32", 4161, 120, 72), ("f32", 4033, 120, 40),
     ("f32", 1025, 60, 1000)])
 def test_affinity_every_tile(dtype, T, E, d):
     rng = np.random.Generator(np.random.PCG64(T + 7 * E + d))
