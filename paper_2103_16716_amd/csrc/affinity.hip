@@ -73,6 +73,25 @@ __device__ inline int64_t source_row(const int32_t *rows, int64_t h_rows, int i)
     return (r >= 0 && r < h_rows) ? r : -1;
 }
 
+// Whether S rows t0 + step(0), ..., t0 + step(N - 1) have a source row in range:
+// bit i of the result. Rows past T repeat the last one, so that the N loads
+// are issued together; a test at each store made every one wait for its own
+// load or branch (a call in bf16, 6000 x 100 x 1000: 12.1 us, now 10.4; 40379 x
+// 26 x 232 through an index: 9.9, now 9.1).
+template <int N, class Step>
+__device__ inline uint32_t rows_in_range(const int32_t *rows, int64_t h_rows, int t0, int T,
+                                         Step step) {
+    if (rows == nullptr) return ~0u;
+    uint32_t ok = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int t = t0 + step(i);
+        const int64_t r = rows[t < T ? t : T - 1];
+        ok |= (uint32_t)(r >= 0 && r < h_rows) << i;
+    }
+    return ok;
+}
+
 // The grid is one-dimensional. Blocks go to the eight XCDs in turn (block L
 // to XCD L % 8); the nn expert tiles of a token tile are placed on one XCD
 // one after another (the same L % 8, consecutive L / 8), so that the token
@@ -233,18 +252,21 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
     }
     // 32x32 accumulator layout: lane holds column lane % 32; register i holds
     // row 8 (i / 4) + 4 (lane / 32) + i % 4.
+    const auto step = [](int i) { return 8 * (i >> 2) + (i & 3); };
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int e = n0 + 32 * (wn * TN + j) + lrow;
-        if (e >= E) continue;
+    for (int x = 0; x < TM; ++x) {
+        const int t0 = m0 + 32 * (wm * TM + x) + 4 * lhalf;
+        const uint32_t ok = rows_in_range<16>(rows, h_rows, t0, T, step);
 #pragma unroll
-        for (int x = 0; x < TM; ++x)
+        for (int j = 0; j < TN; ++j) {
+            const int e = n0 + 32 * (wn * TN + j) + lrow;
+            if (e >= E) continue;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int t = m0 + 32 * (wm * TM + x) + 8 * (i >> 2) + 4 * lhalf + (i & 3);
-                if (t < T)
-                    S[(int64_t)t * E + e] = source_row(rows, h_rows, t) >= 0 ? acc[x][j][i] : 0.0f;
+                const int t = t0 + step(i);
+                if (t < T) S[(int64_t)t * E + e] = (ok >> i & 1) != 0 ? acc[x][j][i] : 0.0f;
             }
+        }
     }
 }
 
@@ -358,11 +380,11 @@ __global__ __launch_bounds__(64 * kSWaves) void affinity_small_kernel(
         // holds row 4 (lane / 16) + i.
         const int e = n0 + 16 * (tile % NJ) + lrow;
         if (e >= E) continue;
+        const int t0 = m0 + 16 * (tile / NJ) + 4 * lq;
+        const uint32_t ok = rows_in_range<4>(rows, h_rows, t0, T, [](int i) { return i; });
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = m0 + 16 * (tile / NJ) + 4 * lq + i;
-            if (t < T) S[(int64_t)t * E + e] = source_row(rows, h_rows, t) >= 0 ? sum[i] : 0.0f;
-        }
+        for (int i = 0; i < 4; ++i)
+            if (t0 + i < T) S[(int64_t)(t0 + i) * E + e] = (ok >> i & 1) != 0 ? sum[i] : 0.0f;
     }
 }
 
