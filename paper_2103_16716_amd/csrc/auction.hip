@@ -1959,8 +1959,9 @@ __global__ __launch_bounds__(kThreads) void update_wide_kernel(Ctx<M> c0) {
 constexpr int kLoopThreads = 512;
 constexpr int kLoopWaves = kLoopThreads / 64;
 constexpr int kLoopCand = 5120;      // bids of a block's experts staged in LDS (12 bytes each)
-constexpr int kLoopCandMin = 4096;
-constexpr int kLoopOwned = 255;      // experts per block (the high byte of a staged position)
+// (at least one step of a list that overflows: a chunk of eight or, with more
+// than 256 experts, four positions per thread)
+__host__ __device__ constexpr int loop_cand_min(int E) { return (E <= 256 ? 8 : 4) * kLoopThreads; }
 constexpr int kLoopWaveBids = 192;   // bids of an expert one wave takes (the block above that)
 constexpr int kLoopToks = 1024;      // positions of a block whose tokens stay in LDS
 constexpr size_t kLoopLdsMax = 79 * 1024;   // two blocks per compute unit
@@ -1982,12 +1983,21 @@ __host__ __device__ inline LoopLds loop_lds(int E, int vbytes, int nb) {
     L.und = off;  off += (size_t)kLoopToks * 2;
     L.scr = off;  off += (size_t)kLoopWaves * 2 * 64 * 8;   // wave scratch, or the histogram
     int cap = (int)((kLoopLdsMax - off) / 12) & ~63;
-    cap = cap > kLoopCand ? kLoopCand : (cap < kLoopCandMin ? kLoopCandMin : cap);
+    cap = cap > kLoopCand ? kLoopCand : (cap < loop_cand_min(E) ? loop_cand_min(E) : cap);
     L.cap = cap;
     L.key = off;  off += (size_t)cap * 8;
     L.pos = off;  off += (size_t)cap * 4;
     L.total = off;
     return L;
+}
+
+// A staged bid's word: its position (below T) in the low bits, the block's
+// index of its expert above them. 256 experts fit beside the largest T, 2048
+// beside positions up to 2^21.
+__host__ __device__ inline int loop_pos_bits(int T) {
+    int b = 1;
+    while (b < 24 && (1 << b) < T) ++b;
+    return b;
 }
 
 // Agent-scope accesses of the data that crosses blocks inside the loop.
@@ -2154,14 +2164,14 @@ __device__ inline uint64_t wave_threshold(const uint64_t (&kk)[NQ], uint64_t b, 
 template <class M, int NQ>
 __device__ inline int loop_update_wave(const Ctx<M> &c, uint64_t (&kk)[NQ], int h,
                                        uint64_t *hold, uint32_t le, const uint64_t *key,
-                                       const uint32_t *pos, int m, int *out, uint64_t *acc,
-                                       uint64_t *ev) {
+                                       const uint32_t *pos, int pb, int m, int *out,
+                                       uint64_t *acc, uint64_t *ev) {
     const int lane = lane_id();
     const int C = c.C;
     for (int i0 = 0; i0 < m; i0 += 64) {
         const int i = i0 + lane;
         const uint32_t at = i < m ? pos[i] : ~0u;
-        const bool mine = i < m && (at >> 24) == le;
+        const bool mine = i < m && (at >> pb) == le;
         const uint64_t bm = __ballot(mine);
         if (bm == 0) continue;
         const uint64_t b = mine ? key[i] : 0ull;
@@ -2193,7 +2203,7 @@ __device__ inline int loop_update_wave(const Ctx<M> &c, uint64_t (&kk)[NQ], int 
         if (mine) {
             if (!keep) o = key_token(b);
             else if (rank >= room) o = rank - room < ne ? key_token(ev[(rank - room) & 63]) : -1;
-            st_agent(&out[at & 0xffffffu], o);
+            st_agent(&out[at & ((1u << pb) - 1u)], o);
         }
         const int h1 = h + nk < C ? h + nk : C;
 #pragma unroll
@@ -2383,7 +2393,7 @@ static_assert(sizeof(LoopMerge) <= kLoopWaves * 2 * 64 * 8, "fits the waves' scr
 template <class M>
 __device__ __attribute__((always_inline)) inline void loop_update_list(
     const Ctx<M> &c, int e, uint32_t le, int n, int *hc, int sel, int *out, const uint64_t *key,
-    const uint32_t *pos, int m, LoopMerge &sm) {
+    const uint32_t *pos, int pb, int m, LoopMerge &sm) {
     uint64_t *gone = sm.u.gone;
     uint16_t *gslot = sm.u.gslot;
     const int tid = threadIdx.x;
@@ -2395,7 +2405,7 @@ __device__ __attribute__((always_inline)) inline void loop_update_list(
     const int m_round = ((m + 63) / 64) * 64;   // (whole waves)
     const uint64_t hk = tid < h ? hold[tid] : 0ull;
     auto entry = [&](int i) -> uint64_t {
-        return i < m && (pos[i] >> 24) == le ? key[i] : 0ull;
+        return i < m && (pos[i] >> pb) == le ? key[i] : 0ull;
     };
     uint32_t mn = ~0u, mx = 0u;
     auto range = [&](uint64_t k) {
@@ -2526,7 +2536,7 @@ __device__ __attribute__((always_inline)) inline void loop_update_list(
                 if (slot < C) hold[slot] = k;
                 low = k < low ? k : low;
             }
-            st_agent(&out[pos[i] & 0xffffffu], o);
+            st_agent(&out[pos[i] & ((1u << pb) - 1u)], o);
         }
     }
     low = wave_min_u64(low);
@@ -2597,6 +2607,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
     const bool narrow = c.E <= 256;
     const int epl = narrow ? 8 : 4, ebits = narrow ? 8 : 16;
     const uint32_t emask = narrow ? 0xffu : 0xffffu;
+    const int pb = loop_pos_bits(c.T);
     const int64_t base = (int64_t)blk * per;
     const bool in_lds = per <= kLoopToks;
     const int pe = (c.E + nb - 1) / nb;
@@ -2785,7 +2796,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
             for (; hit != 0; hit &= hit - 1) {
                 const int q = __ffs((int)hit) - 1;
                 const int i = (int)((uint32_t)(w >> (ebits * q)) & emask) - e_lo;
-                if (f < L.cap) pos[f] = (uint32_t)(at + q) | ((uint32_t)i << 24);
+                if (f < L.cap) pos[f] = (uint32_t)(at + q) | ((uint32_t)i << pb);
                 ++f;
                 atomicAdd(&lec[i], 1);
             }
@@ -2808,8 +2819,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         if constexpr (NQ > 0) {
             // An expert per wave, or the block for those with many bids.
             // More bids than the list holds: a chunk per thread at a time (at
-            // most 8 kLoopThreads bids), each merged before the next.
-            static_assert(8 * kLoopThreads <= kLoopCandMin, "one step fits the list");
+            // most loop_cand_min of them), each merged before the next.
             const bool over = s_m > L.cap;
             for (int k0 = 0;; k0 += kLoopThreads) {
                 if (over) {
@@ -2824,7 +2834,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
                 }
                 const int mt = s_m;
                 for (int i = tid; i < mt; i += kLoopThreads)
-                    key[i] = ld_agent(&bkey[pos[i] & 0xffffffu]);
+                    key[i] = ld_agent(&bkey[pos[i] & ((1u << pb) - 1u)]);
                 for (int i0 = 0; i0 < owned; i0 += kLoopWaves) {
                     const int i = i0 + wave;
                     const bool take = i < owned && lec[i] > 0 && lec[i] <= kLoopWaveBids;
@@ -2843,7 +2853,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
                     if (i0 == 0) __syncthreads();   // the keys
                     if (take) {
                         const int h1 = loop_update_wave<M, NQ>(c, kk, h, hold, (uint32_t)i, key, pos,
-                                                           mt, out, scr, scr + 64);
+                                                               pb, mt, out, scr, scr + 64);
                         if (h1 == c.C) {   // full: the price is the lowest held bid
                             uint64_t lowest = ~0ull;
 #pragma unroll
@@ -2864,7 +2874,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
                     if (ne <= kLoopWaveBids) continue;
                     const int h = hc[i];
                     loop_update_list<M>(c, e_lo + i, (uint32_t)i, ne, &hc[i], hs[i], out, key, pos,
-                                        mt, merge);
+                                        pb, mt, merge);
                     if (tid == 0) s_out += ne - (hc[i] - h);
                     __syncthreads();
                 }
@@ -6345,9 +6355,10 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     const int bid_blocks = (int)((c.T + kBidTile - 1) / kBidTile);   // one tile of the list each
     const size_t bid_bytes = bid_smem(c.E, (int)sizeof(value_t)).total;
     int upd_blocks = c.E < 2048 ? c.E : 2048;
-    // Round loop (every block of the grid must be resident at once): half the
-    // compute units for a single problem, a share of them for a batch's
-    // (a batch larger than the device holds skips it).
+    // Round loop (every block of a problem must be resident at once): half the
+    // compute units for a single problem, a share of them for a batch's. A
+    // block on its own waits for nobody, so a batch larger than the device
+    // holds runs with one block a problem.
     int coop_blocks = 0;
     size_t loop_bytes = 0;
     constexpr int GL = G < 8 ? 8 : G;   // (its lanes per row: a summary takes eight)
@@ -6360,16 +6371,23 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
         int nb = cus <= 0 ? 0 : (B == 1 ? cus / 2 : cus / B);
         if (nb > kLoopMaxBlocks) nb = kLoopMaxBlocks;
         if (nb == 0 && cus > 0) nb = 1;
-        if (nb > 0 && (c.E + nb - 1) / nb <= kLoopOwned) {
+        // Staged bids name their expert beside their position (experts of more
+        // than kLoopThreads tokens stage none): any E whose scores fit the
+        // memory.
+        const bool names = c.C > kLoopThreads ||
+                           (nb > 0 && (c.E + nb - 1) / nb <= (1ll << (32 - loop_pos_bits(c.T))));
+        if (nb > 0 && names) {
             loop_bytes = loop_lds(c.E, (int)sizeof(value_t), nb).total;
             if (lds_optin(dev, fn, loop_bytes) == hipSuccess) {
                 const int per_cu = occupancy(dev, fn, kLoopThreads, loop_bytes);
-                if ((int64_t)nb * B <= (int64_t)cus * per_cu) coop_blocks = nb;
+                if (nb == 1 || (int64_t)nb * B <= (int64_t)cus * per_cu) coop_blocks = nb;
             } else {
                 (void)hipGetLastError();
-                debug_note("round loop LDS opt-in refused", hipErrorInvalidValue);
             }
         }
+        if (coop_blocks == 0)
+            debug_note("no round loop: large rounds are launched, the last slot's tail is slow",
+                       hipErrorInvalidConfiguration);
     }
     // A round of the loop costs a single problem about 10 us whatever the few
     // hundred bids; one of the engine grows with them. The engine taking over

@@ -27,6 +27,8 @@ def _scores(T, E, kind, seed):
     S = wl.random_scores(T, E, seed)
     if kind == "crowd":      # every token wants the same expert first
         S[:, E // 2] += 6.0
+    if kind == "eight":      # eight experts everyone prefers: many large rounds
+        S[:, :8] += 3.0
     if kind == "tied":       # many equal scores, also at the end of a summary
         S = np.round(S * 4.0) / np.float32(4.0)
     if kind == "close":      # scores that differ in their last bits only
@@ -72,3 +74,23 @@ def test_optimality_bound(T, E, kind):
     S = Sh.astype(np.float64)
     gap = oracle.dual_bound(S, p) - oracle.objective(S, a)
     assert gap <= T * eps_expected(Sh, 1e-4) + rounding_slack(T, S, p)
+
+
+@pytest.mark.parametrize("B,T,E", [(160, 4096, 256), (640, 2560, 64), (128, 4096, 512)])
+def test_large_batches_keep_the_loop(B, T, E):
+    """Batches that leave a problem few blocks, down to one that owns every
+    expert, or that exceed the device run their large rounds in the loop too.
+    The problems are those of a batch of four, so the results repeat and the
+    bids placed in the engine (rounds of at most 256 tokens) add up. One phase,
+    so one slot: without the loop it would end in the tail, with no bid in the
+    engine."""
+    kw = dict(eps_initial=0.02, eps_final=0.02)
+    four = torch.stack([dev(_scores(T, E, "eight", seed=T + E + b)) for b in range(4)])
+    ref = pb.assign_batched(four, **kw)
+    assert ref.stats.phases == 1 and ref.stats.engine_bids > 0
+    res = pb.assign_batched(four.repeat(B // 4, 1, 1), **kw)
+    for name in ("assign", "perm", "prices"):
+        x, y = getattr(res, name), getattr(ref, name)
+        assert torch.equal(x.view(B // 4, 4, -1), y.view(1, 4, -1).expand(B // 4, 4, -1))
+    assert res.stats.bids == B // 4 * ref.stats.bids
+    assert res.stats.engine_bids == B // 4 * ref.stats.engine_bids
