@@ -1949,13 +1949,28 @@ __global__ __launch_bounds__(kThreads) void update_wide_kernel(Ctx<M> c0) {
 // by bit over the block (two bits a barrier) took 10-20 us, the histograms
 // 4-6; reading the list from registers instead of LDS spilled.
 //
-// Every block of the grid must be resident at once. The launch follows the
-// stream's previous kernels, so on the idle device it is (the host checks
-// the occupancy: two blocks to a compute unit, so that four solves on
-// streams of their own fit together). The waits are bounded: a block never scheduled ends the solve
-// with an internal error, not a hang. (A cooperative launch would guarantee
+// Every block of a problem must be resident at once, also beside the loops of
+// other streams. Compute units hold two blocks each, an XCD 64. Four loops
+// (a process has four hardware queues by default) cannot starve each other:
+//   - one of at most 128 blocks in all (single solves, batches of up to
+//     seven) has at most 16 on an XCD;
+//   - one of a larger batch has all blocks of a problem, at most 16, on one
+//     XCD, in turn: an XCD starts them in order, so only the last problem it
+//     has started there can be waiting for blocks, with at most 15 of them;
+//   - a block alone on its problem waits for nobody.
+// So whatever has not started on an XCD finds at most 63 blocks waiting there,
+// and the others end by themselves. (A block of the greedy routing takes as much
+// room, and up to 24 of a routing wait on an XCD: two solves fit beside one
+// routing, one beside two.) Batches of up to 256 blocks spread over the XCDs
+// left this to luck, since three of them fill the device in part; 128 blocks
+// for every batch took 5% longer for 64 problems of T = 4096, E = 64 and 14%
+// for 64 of T = 8192, E = 16, a problem to an XCD takes as long as before. The
+// waits are bounded all the same: a block never scheduled ends the solve with
+// an internal error, not a hang. (A cooperative launch would guarantee
 // residency, but costs 20-40 us here against 2.5 us for a plain one.) The
 // launch returns at once when there is nothing to do.
+constexpr int kXcds = 8;         // blocks go to the XCDs in turn
+constexpr int kLoopLocal = 16;   // most blocks of a problem placed on one XCD
 constexpr int kLoopThreads = 512;
 constexpr int kLoopWaves = kLoopThreads / 64;
 constexpr int kLoopCand = 5120;      // bids of a block's experts staged in LDS (12 bytes each)
@@ -2024,13 +2039,13 @@ __device__ inline void st_price(int64_t *p, int64_t v) { st_agent(p, v); }
 // the words of seq. `payload` (31 bits, thread 0's) reaches every block:
 // cnt[k] is block k's. Returns false when the wait gave up.
 constexpr uint32_t kLoopErr = 0x80000000u;   // payload bit: the block saw an error
-__device__ inline bool loop_barrier(uint64_t *flags, uint32_t seq, int nb, uint32_t payload,
-                                    int *cnt, SolveCtrl *ctrl, uint32_t poll_limit) {
+__device__ inline bool loop_barrier(uint64_t *flags, uint32_t seq, int nb, int blk,
+                                    uint32_t payload, int *cnt, SolveCtrl *ctrl, uint32_t poll_limit) {
     __shared__ int ok;
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores have arrived
     __syncthreads();
     uint64_t *w = flags + (seq & 1) * kLoopMaxBlocks;
-    if (threadIdx.x == 0) st_agent(w + blockIdx.x, ((uint64_t)seq << 32) | payload);
+    if (threadIdx.x == 0) st_agent(w + blk, ((uint64_t)seq << 32) | payload);
     if (threadIdx.x < 64) {
         const int l = threadIdx.x;
         uint64_t a = 0, b = 0;
@@ -2556,17 +2571,23 @@ __device__ __attribute__((always_inline)) inline void loop_update_list(
 
 // NQ: holders of an expert per lane of a wave (C <= 64 NQ); 0: experts of more
 // than kLoopThreads tokens, merged by loop_update_block.
+// `local_batch`: 0, the grid is (blocks, problems); a batch's size, its problems
+// each on an XCD of their own (kLoopLocal).
 // `free_rounds`: the launch's first rounds that do not look at max_rounds
 // (the rounds a phase's first launches always run).
 template <class M, int G, int NQ>   // G >= 8
-__global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, int max_wide,
-                                                                  int free_rounds,
+__global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, int local_batch,
+                                                                  int max_wide, int free_rounds,
                                                                   int32_t max_rounds,
                                                                   uint32_t poll_limit) {
-    const Ctx<M> c = c0.at(blockIdx.y);
+    const bool local = local_batch > 0;
+    const int prob = local ? blockIdx.y * kXcds + blockIdx.x % kXcds : blockIdx.y;
+    if (local && prob >= local_batch) return;
+    const Ctx<M> c = c0.at(prob);
     using value_t = typename M::value_t;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int nb = gridDim.x, blk = blockIdx.x;
+    const int nb = local ? gridDim.x / kXcds : gridDim.x;
+    const int blk = local ? blockIdx.x / kXcds : blockIdx.x;
     const LoopLds L = loop_lds(c.E, (int)sizeof(value_t), nb);
     value_t *pr = reinterpret_cast<value_t *>(smem_raw + L.pr);
     int *hc = reinterpret_cast<int *>(smem_raw + L.hc);
@@ -2751,7 +2772,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
             }
         }
         ++seq;
-        if (!loop_barrier(c.flags, seq, nb, (uint32_t)m | (s_err ? kLoopErr : 0u), cnt, ctrl,
+        if (!loop_barrier(c.flags, seq, nb, blk, (uint32_t)m | (s_err ? kLoopErr : 0u), cnt, ctrl,
                           poll_limit))
             return;
         // (2) The bids of this block's experts: the filled positions of every
@@ -2900,7 +2921,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
             }
         }
         ++seq;
-        if (!loop_barrier(c.flags, seq, nb, (uint32_t)s_out, cnt, ctrl, poll_limit)) return;
+        if (!loop_barrier(c.flags, seq, nb, blk, (uint32_t)s_out, cnt, ctrl, poll_limit)) return;
         if (tid < 64) {
             int v = cnt[lane] + cnt[lane + 64];
 #pragma unroll
@@ -2948,7 +2969,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
     }
     if (n > 0 && !early) {
         ++seq;
-        if (!loop_barrier(c.flags, seq, nb, (uint32_t)m, cnt, ctrl, poll_limit)) return;
+        if (!loop_barrier(c.flags, seq, nb, blk, (uint32_t)m, cnt, ctrl, poll_limit)) return;
         if (tid < 64) {
             const int lane = tid;
             int before = 0;
@@ -6355,11 +6376,11 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     const int bid_blocks = (int)((c.T + kBidTile - 1) / kBidTile);   // one tile of the list each
     const size_t bid_bytes = bid_smem(c.E, (int)sizeof(value_t)).total;
     int upd_blocks = c.E < 2048 ? c.E : 2048;
-    // Round loop (every block of a problem must be resident at once): half the
-    // compute units for a single problem, a share of them for a batch's. A
-    // block on its own waits for nobody, so a batch larger than the device
-    // holds runs with one block a problem.
+    // Round loop: half the compute units for a single problem or, shared out,
+    // up to seven; a larger batch's problems take a share of all of them, on
+    // one XCD each (see kLoopLocal).
     int coop_blocks = 0;
+    bool loop_local = false;
     size_t loop_bytes = 0;
     constexpr int GL = G < 8 ? 8 : G;   // (its lanes per row: a summary takes eight)
     const auto loop_fn = c.C <= 256 ? &round_loop_kernel<M, GL, 4>
@@ -6368,9 +6389,11 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     {
         const int cus = facts.cus;
         const void *fn = reinterpret_cast<const void *>(loop_fn);
-        int nb = cus <= 0 ? 0 : (B == 1 ? cus / 2 : cus / B);
-        if (nb > kLoopMaxBlocks) nb = kLoopMaxBlocks;
+        int nb = cus <= 0 ? 0 : (B < 8 ? cus / 2 / B : cus / B);
+        const int most = B < 8 ? kLoopMaxBlocks : kLoopLocal;
+        if (nb > most) nb = most;
         if (nb == 0 && cus > 0) nb = 1;
+        loop_local = B >= 8 && nb > 1;
         // Staged bids name their expert beside their position (experts of more
         // than kLoopThreads tokens stage none): any E whose scores fit the
         // memory.
@@ -6416,7 +6439,10 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
             hipLaunchKernelGGL(update_wide_kernel<M>, dim3(upd_blocks, B), dim3(kThreads), 0, s, c);
         }
         if (coop_blocks > 0)
-            hipLaunchKernelGGL(loop_fn, dim3(coop_blocks, B), dim3(kLoopThreads), loop_bytes, s, c,
+            hipLaunchKernelGGL(loop_fn,
+                               loop_local ? dim3(kXcds * coop_blocks, (B + kXcds - 1) / kXcds)
+                                          : dim3(coop_blocks, B),
+                               dim3(kLoopThreads), loop_bytes, s, c, loop_local ? B : 0,
                                kWideLoopRounds + (first - wr), first - wr, p.max_rounds,
                                barrier_polls());
         if (engine) {

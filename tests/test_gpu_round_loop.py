@@ -94,3 +94,40 @@ def test_large_batches_keep_the_loop(B, T, E):
         assert torch.equal(x.view(B // 4, 4, -1), y.view(1, 4, -1).expand(B // 4, 4, -1))
     assert res.stats.bids == B // 4 * ref.stats.bids
     assert res.stats.engine_bids == B // 4 * ref.stats.engine_bids
+
+
+@pytest.mark.parametrize("B,T,E", [(24, 4096, 64), (3, 8192, 128), (1, 16384, 128), (64, 8192, 16)])
+def test_four_solves_at_once(B, T, E):
+    """Four solves on streams of their own, their loops' waiting blocks side by
+    side: each ends balanced, with the results it has alone. (The last shape
+    has more positions a block than its token list holds.)"""
+    S = [torch.stack([dev(_scores(T, E, "normal", seed=1000 * i + b % 5)) for b in range(B)])
+         for i in range(4)]
+    one = [pb.assign_batched(s) for s in S]
+    ws = [torch.empty(pb.assign_batched_workspace_size(B, T, E), dtype=torch.uint8, device="cuda")
+          for _ in S]
+    out = [[torch.empty_like(x) for x in (r.assign, r.perm, r.prices)] for r in one]
+    streams = [torch.cuda.Stream() for _ in S]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for s, w, o, st in zip(S, ws, out, streams):
+            pb.assign_batched(s, workspace=w, out_assign=o[0], out_perm=o[1], out_prices=o[2],
+                              sync_stats=False, stream=st)
+    for w, o, st, r in zip(ws, out, streams, one):
+        code, stats = pb.assign_status(w, T, E, B=B, stream=st)
+        assert code == pb.BASE_OK and stats.converged == 1
+        for x, y in zip(o, (r.assign, r.perm, r.prices)):
+            assert torch.equal(x, y)
+
+
+def test_tokens_of_a_block_beyond_its_list():
+    """Blocks with more positions than their token list in LDS holds (two blocks
+    for 8192 tokens) against the problems' own solves (128 blocks)."""
+    B, T, E = 96, 8192, 16
+    S = torch.stack([dev(_scores(T, E, ("normal", "eight", "crowd")[b % 3], seed=b)) for b in range(6)])
+    res = pb.assign_batched(S.repeat(B // 6, 1, 1))
+    for b in range(6):
+        ref = pb.assign(S[b].contiguous())
+        for k in (b, b + 48, B - 6 + b):
+            for name in ("assign", "perm", "prices"):
+                assert torch.equal(getattr(res, name)[k], getattr(ref, name))
