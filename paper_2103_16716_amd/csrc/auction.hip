@@ -2245,23 +2245,75 @@ struct LoopSelect {
     int sel_digit, sel_count, need, kept, evicted, taken;
 };
 
-// The whole block merges expert e's n bids into its h holders, for the
-// expert with more bids or holders than one wave takes: an MSD radix select
-// of the C-th largest key over for_bids (all of the expert's bids, a call
-// fn(position, key, valid) with wave-uniform trips) and the holder table.
-// The kept keys go to the other holder table, the displaced holders first to
-// the expert's bucket, then to the out positions of the kept bids.
+// Where a block-wide merge finds an expert's bids and leaves its displaced
+// holders, all in the expert's bucket (room for cap >= C keys).
+struct LoopBids {
+    const uint64_t *key;   // their keys (null: through their positions)
+    const uint32_t *at;    // their positions (null: more than the bucket notes)
+    uint32_t *gone;        // room for the displaced holders' tokens
+};
+
+// The whole block merges expert e's n bids into its h holders, for experts of
+// more than kLoopThreads tokens: an MSD radix select of the C-th largest key.
+// The kept keys go to the other holder table, the displaced holders' tokens
+// first to src.gone, then to the out positions of the kept bids. `rescan` calls
+// fn(position, key) for every bid when src.at is null.
+//
+// Bound by the passes over the keys, each a few dependent loads long: the bids
+// are collected once (finding them in the bid table again in every pass, and
+// holders one load at a time: T = 2^20, E = 64 48.5 ms, now 13.5; T = 262144, E =
+// 128 12.5, now 6.6; T = 65536, E = 64 6.5, now 4.8), two loads in flight a
+// thread (four: 5% slower up to T = 262144, 5% faster at 2^20; staging the keys
+// in LDS gained nothing). Launching the first three rounds over the whole
+// device instead was no faster at any of these sizes.
 template <class M, class F>
-__device__ __attribute__((always_inline)) inline void loop_update_block(const Ctx<M> &c, int e, int n, int *hc, int *hs, int *out,
-                                  LoopSelect &sm, F for_bids) {
+__device__ __attribute__((always_inline)) inline void loop_update_block(
+    const Ctx<M> &c, int e, int n, int *hc, int *hs, int *out, const uint64_t *bkey,
+    const LoopBids &src, LoopSelect &sm, F rescan) {
     using value_t = typename M::value_t;
     const int tid = threadIdx.x;
     const int C = c.C;
     const int h = *hc, sel = *hs;
     uint64_t *hold = c.holders + (int64_t)sel * c.T + (int64_t)e * C;
     uint64_t *alt = c.holders + (int64_t)(sel ^ 1) * c.T + (int64_t)e * C;
-    uint64_t *gone = c.bucket + (int64_t)e * c.cap;   // (cap >= C)
     value_t *price = c.prices + e;
+    constexpr int kU = 2;   // loads in flight per thread
+    auto for_holders = [&](auto fn) {
+        for (int i0 = tid; i0 < h; i0 += kU * kLoopThreads) {
+            uint64_t k[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int i = i0 + u * kLoopThreads;
+                if (i < h) k[u] = hold[i];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (i0 + u * kLoopThreads < h) fn(k[u]);
+        }
+    };
+    auto for_bids = [&](auto fn) {
+        if (src.at == nullptr) {
+            rescan(fn);
+            return;
+        }
+        for (int i0 = tid; i0 < n; i0 += kU * kLoopThreads) {
+            uint32_t at[kU];
+            uint64_t k[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int i = i0 + u * kLoopThreads;
+                if (i < n) at[u] = src.at[i];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int i = i0 + u * kLoopThreads;
+                if (i < n) k[u] = src.key != nullptr ? src.key[i] : ld_agent(&bkey[at[u]]);
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (i0 + u * kLoopThreads < n) fn(at[u], k[u]);
+        }
+    };
     uint64_t tmin = ~0ull, tmax = 0;
     auto range = [&](uint64_t k, bool v) {
         if (v) {
@@ -2282,8 +2334,8 @@ __device__ __attribute__((always_inline)) inline void loop_update_block(const Ct
         }
     };
     auto for_all = [&](auto fn) {
-        for (int i = tid; i < h; i += kLoopThreads) fn(hold[i], true);
-        for_bids([&](uint32_t, uint64_t k, bool v) { fn(k, v); });
+        for_holders([&](uint64_t k) { fn(k, true); });
+        for_bids([&](uint32_t, uint64_t k) { fn(k, true); });
     };
     __syncthreads();
     if (tid == 0) {
@@ -2294,15 +2346,15 @@ __device__ __attribute__((always_inline)) inline void loop_update_block(const Ct
     __syncthreads();
     if (h + n <= C) {
         // Room for every bid.
-        for_bids([&](uint32_t at, uint64_t k, bool v) {
-            if (!v) return;
+        const bool full = h + n == C;
+        for_bids([&](uint32_t at, uint64_t k) {
             const int s = h + atomicAdd(&sm.taken, 1);
             if (s < C) hold[s] = k;
             st_agent(&out[at], -1);
+            range(k, full);
         });
-        __syncthreads();
-        if (h + n == C) {
-            for (int i = tid; i < C; i += kLoopThreads) range(hold[i], true);
+        if (full) {
+            for_holders([&](uint64_t k) { range(k, true); });
             range_done();
         }
         __syncthreads();
@@ -2351,27 +2403,25 @@ __device__ __attribute__((always_inline)) inline void loop_update_block(const Ct
         __syncthreads();
     }
     const uint64_t kstar = at_min ? sm.kmin : prefix;   // keys are unique: a key
-    for (int i = tid; i < h; i += kLoopThreads) {
-        const uint64_t k = hold[i];
+    for_holders([&](uint64_t k) {
         if (k >= kstar) {
             const int at = atomicAdd(&sm.kept, 1);
             if (at < C) alt[at] = k;
         } else {
             const int at = atomicAdd(&sm.evicted, 1);
-            if (at < c.cap) gone[at] = k;
+            if (at < C) src.gone[at] = (uint32_t)key_token(k);
         }
-    }
+    });
     __threadfence_block();
     __syncthreads();
     const int room = C - h, ne = sm.evicted;
-    for_bids([&](uint32_t at, uint64_t k, bool v) {
-        if (!v) return;
+    for_bids([&](uint32_t at, uint64_t k) {
         int o = key_token(k);
         if (k >= kstar) {
             const int w = atomicAdd(&sm.kept, 1);
             if (w < C) alt[w] = k;
             const int r = atomicAdd(&sm.taken, 1) - room;
-            o = r < 0 ? -1 : (r < ne && r < c.cap ? key_token(gone[r]) : -1);
+            o = r < 0 ? -1 : (r < ne && r < C ? (int)src.gone[r] : -1);
         }
         st_agent(&out[at], o);
     });
@@ -2804,6 +2854,9 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
             if (left <= 0) return 0;
             return ld_agent(reinterpret_cast<const uint64_t *>(bexp + (narrow ? at : 2 * at)));
         };
+        auto bucket_at = [&](int e) {
+            return reinterpret_cast<uint32_t *>(c.bucket + (int64_t)e * c.cap) + c.cap;
+        };
         // Collects the chunk's bids for this block's experts.
         auto take_chunk = [&](uint64_t w, int at, int left) {
             uint32_t hit = 0;
@@ -2813,13 +2866,18 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
                 hit |= (uint32_t)(i < (uint32_t)owned && q < left) << q;
             }
             if (hit == 0) return;
-            int f = atomicAdd(&s_m, __popc(hit));
+            int f = NQ > 0 ? atomicAdd(&s_m, __popc(hit)) : 0;
             for (; hit != 0; hit &= hit - 1) {
                 const int q = __ffs((int)hit) - 1;
                 const int i = (int)((uint32_t)(w >> (ebits * q)) & emask) - e_lo;
-                if (f < L.cap) pos[f] = (uint32_t)(at + q) | ((uint32_t)i << pb);
-                ++f;
-                atomicAdd(&lec[i], 1);
+                if constexpr (NQ > 0) {
+                    if (f < L.cap) pos[f] = (uint32_t)(at + q) | ((uint32_t)i << pb);
+                    ++f;
+                    atomicAdd(&lec[i], 1);
+                } else {   // to the upper half of the expert's bucket
+                    const int k = atomicAdd(&lec[i], 1);
+                    if (k < c.cap) bucket_at(e_lo + i)[k] = (uint32_t)(at + q);
+                }
             }
         };
         constexpr int kU = 8;
@@ -2907,13 +2965,25 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
                 if (ne == 0) continue;
                 const int e = e_lo + i;
                 const int h = hc[i];
-                loop_update_block<M>(c, e, ne, &hc[i], &hs[i], out, sel, [&](auto fn) {
+                // The bids' keys are copied to the lower half of the bucket, read
+                // through their positions when that is too short for them, and
+                // found again in every pass when not even those fit.
+                uint32_t *at = bucket_at(e);
+                uint64_t *low = c.bucket + (int64_t)e * c.cap;
+                LoopBids src{nullptr, ne <= c.cap ? at : nullptr,
+                               reinterpret_cast<uint32_t *>(low)};
+                if (ne <= c.cap / 2) {
+                    for (int k = tid; k < ne; k += kLoopThreads) low[k] = ld_agent(&bkey[at[k]]);
+                    src.key = low;
+                    src.gone = at + c.cap / 2;   // (at most ne)
+                }
+                loop_update_block<M>(c, e, ne, &hc[i], &hs[i], out, bkey, src, sel, [&](auto fn) {
                     for (int k = tid; k < total; k += kLoopThreads) {
-                        int at, left;
-                        const uint64_t w = load_chunk(k, at, left);
+                        int p, left;
+                        const uint64_t w = load_chunk(k, p, left);
                         for (int q = 0; q < left; ++q)
                             if ((int)((uint32_t)(w >> (ebits * q)) & emask) == e)
-                                fn((uint32_t)(at + q), ld_agent(&bkey[at + q]), true);
+                                fn((uint32_t)(p + q), ld_agent(&bkey[p + q]));
                     }
                 });
                 if (tid == 0) s_out += ne - (hc[i] - h);

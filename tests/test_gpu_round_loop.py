@@ -58,6 +58,10 @@ def test_same_rounds_as_the_single_workgroup_solver(monkeypatch, T, E, kind):
 @pytest.mark.parametrize("T,E,kind", [(16384, 32, "crowd"), (6000, 600, "normal"),
                                       (6000, 600, "crowd"), (12288, 8, "crowd"),
                                       (4097, 17, "crowd"),
+                                      # experts of more than 512 tokens: bids with their
+                                      # keys in the bucket, with positions only, beyond it
+                                      (16416, 32, "normal"), (4104, 8, "eight"),
+                                      (16416, 32, "crowd"), (135200, 260, "normal"),
                                       # the score summaries: rows of part groups and
                                       # of whole ones, ties at the 8th and 9th score
                                       (264, 33, "tied"), (512, 64, "tied"), (2000, 100, "close"),
