@@ -275,6 +275,9 @@ __device__ inline int lane_id() { return threadIdx.x & 63; }
 // The thread's index as a value the compiler knows nothing about: parts of a
 // kernel that run in turn inside a loop use one each, so that their addresses
 // are formed where they are used and not kept in registers across the others.
+// (Also in the merges of the round loop and of the single-workgroup solver:
+// without it 65 and 23 spilled registers in integer solves, 8 and 13 with it;
+// T = 4096, E = 16 on narrow int16 scores 885 -> 834 us.)
 __device__ inline int opaque_tid() {
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
@@ -2181,7 +2184,7 @@ __device__ inline int loop_update_wave(const Ctx<M> &c, uint64_t (&kk)[NQ], int 
                                        uint64_t *hold, uint32_t le, const uint64_t *key,
                                        const uint32_t *pos, int pb, int m, int *out,
                                        uint64_t *acc, uint64_t *ev) {
-    const int lane = lane_id();
+    const int lane = opaque_tid() & 63;
     const int C = c.C;
     for (int i0 = 0; i0 < m; i0 += 64) {
         const int i = i0 + lane;
@@ -2461,7 +2464,7 @@ __device__ __attribute__((always_inline)) inline void loop_update_list(
     const uint32_t *pos, int pb, int m, LoopMerge &sm) {
     uint64_t *gone = sm.u.gone;
     uint16_t *gslot = sm.u.gslot;
-    const int tid = threadIdx.x;
+    const int tid = opaque_tid();
     const int lane = tid & 63, wave = tid >> 6;
     const int C = c.C;
     const int h = *hc;
@@ -2788,7 +2791,7 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
             const int nu = s_und;
             // Whole rows, G lanes per token, two rows in flight.
             constexpr int kGroups = kLoopThreads / G;
-            constexpr int kRows = 2;
+            constexpr int kRows = M::kInteger ? 1 : 2;
             const int per_wave = 64 / G;
             const int ru = ((nu + per_wave - 1) / per_wave) * per_wave;
             for (int j0 = tid / G; j0 < ru; j0 += kGroups * kRows) {
@@ -5039,7 +5042,7 @@ template <int NQ>
 __device__ inline int small_merge(uint64_t *h, int ce, int C, const uint64_t *bids,
                                   uint64_t *scratch, int nb, int T, int *nxt, int *nnext,
                                   SolveCtrl *ctrl) {
-    const int lane = lane_id();
+    const int lane = opaque_tid() & 63;
     for (int j0 = 0; j0 < nb; j0 += 64) {
         const int k = nb - j0 < 64 ? nb - j0 : 64;
         const uint64_t b = lane < k ? bids[j0 + lane] : 0ull;
@@ -5476,7 +5479,10 @@ __device__ __attribute__((always_inline)) inline void small_rounds(const Ctx<M> 
 // not wait for each other between the steps, and a step costs no launch:
 // with a launch for each (rounds, exchange matrix, finish, four times over)
 // the solve of T = 512, E = 8 took 154 us, 134 this way, and 256 shuffled
-// problems of T = 2048, E = 128 with their rows routed 3600, 3455 this way.
+// problems of T = 2048, E = 128 with their rows routed 3600, 3455 this way. The
+// parts share 128 registers a thread: at E > 128 the exchange matrix takes half
+// of them and 186 values are spilled, still faster than the launches (256 x (2048
+// x 256) 7.3 ms, 3.8 this way); up to E = 128 it is at most two.
 template <class M, int G>
 __global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, AssignParams p,
                                                                     int ssp_cap, int nslots,
@@ -5484,6 +5490,10 @@ __global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, A
     constexpr int Ep = 8 * G > 256 ? 256 : (8 * G < 32 ? 32 : 8 * G);   // E <= kSmallE = 256
     const Ctx<M> c = c0.at(blockIdx.y);
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    if constexpr (M::kInteger) {   // no shortest-path finish: one call to the end
+        small_rounds<M, G>(c, p, 0, smem_raw);
+        return;
+    }
     __shared__ int s_done;
     for (int slot = 0; slot < nslots; ++slot) {
         const int cap = slot < nslots - 1 ? ssp_cap : 0;
@@ -5493,14 +5503,12 @@ __global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, A
         __syncthreads();
         if (s_done) return;
         if constexpr (!M::kInteger) {
-            if (cap > 0) {
-                int n = 0;
-                if (ssp_pending<M>(c, &n)) {   // (uniform: every thread reads the same words)
-                    ssp_build_run<M, Ep>(c);
-                    __syncthreads();
-                    ssp_run<M, Ep>(c, c.ssp_cap, fallbacks, smem_raw);
-                    __syncthreads();
-                }
+            int n = 0;
+            if (cap > 0 && ssp_pending<M>(c, &n)) {   // (uniform: the same words for every thread)
+                ssp_build_run<M, Ep>(c);
+                __syncthreads();
+                ssp_run<M, Ep>(c, c.ssp_cap, fallbacks, smem_raw);
+                __syncthreads();
             }
         }
     }
