@@ -167,6 +167,20 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
     // invalid source rows, read a valid row; their outputs are not stored
     // (or stored as zero).
     const int cu = (tid % kUnits) ^ ((tid / kUnits) & 7);
+    const int wm = wave % kWm;
+    const int wn = wave / kWm;
+    const int lrow = lane & 31;
+    const int lhalf = lane >> 5;
+    // 32x32 accumulator layout: lane holds column lane % 32; register i holds
+    // row 8 (i / 4) + 4 (lane / 32) + i % 4. The checks of a wave's 32 rows are
+    // loaded here, beside the other indices, and not between the last product
+    // and its store (64 x 64 tiles, 300000 x 8 x 16 through an index: 20.1 us, 17.0
+    // this way; with 64 rows a wave it is 19.0 and 20.9).
+    const auto step = [](int i) { return 8 * (i >> 2) + (i & 3); };
+    const auto checks = [&](int x) {
+        return rows_in_range<16>(rows, h_rows, m0 + 32 * (wm * TM + x) + 4 * lhalf, T, step);
+    };
+    const uint32_t early = TM == 1 ? checks(0) : 0u;
     const typename In::elem_t *ga[kSa], *gb[kSb];
 #pragma unroll
     for (int i = 0; i < kSa; ++i) {
@@ -181,7 +195,7 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
         const int er = n0 + r < E ? n0 + r : E - 1;
         gb[i] = W + (int64_t)er * d + cu * In::kPer;
     }
-    const int nk = (d + kPK - 1) / kPK;
+    const int nk = kSt == 1 ? 1 : (d + kPK - 1) / kPK;
     const int rot = mt % nk;
     auto chunk_of = [&](int kc) { return kc + rot < nk ? kc + rot : kc + rot - nk; };
     auto issue = [&](int kc, int st) {
@@ -200,10 +214,6 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
                 in ? (const void *)(gb[i] + k) : (const void *)&zero_unit,
                 (BASE_LDS void *)(base + BM * kChunk + (i * kThreads + wave * 64) * 16), 16, 0, 0);
     };
-    const int wm = wave % kWm;
-    const int wn = wave / kWm;
-    const int lrow = lane & 31;
-    const int lhalf = lane >> 5;
     f32x16_t acc[TM][TN];
 #pragma unroll
     for (int x = 0; x < TM; ++x)
@@ -211,6 +221,7 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[x][j][i] = 0.0f;
+    if (kSt == 1) issue(0, 0);
 #pragma unroll
     for (int st = 0; st < kSt - 1; ++st)
         if (st < nk) issue(st, st);
@@ -219,16 +230,17 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
         // Chunk kc has landed once at most the later chunks' loads are in
         // flight; after the barrier every wave's part of it is in LDS and
         // every wave is done with the stage refilled next.
-        if (kc + kSt - 2 < nk) wait_vmcnt<(kSa + kSb) * (kSt - 2)>();
+        if (kSt > 1 && kc + kSt - 2 < nk) wait_vmcnt<(kSa + kSb) * (kSt > 1 ? kSt - 2 : 0)>();
         else wait_vmcnt<0>();
         bare_barrier();
-        if (kc + kSt - 1 < nk) issue(kc + kSt - 1, st == 0 ? kSt - 1 : st - 1);
+        if (kSt > 1 && kc + kSt - 1 < nk) issue(kc + kSt - 1, st == 0 ? kSt - 1 : st - 1);
         const unsigned char *A = lds + st * kStage;
         const unsigned char *B = A + BM * kChunk;
         st = st + 1 < kSt ? st + 1 : 0;
         // Two units of every row per step, one per half wave.
 #pragma unroll
         for (int ks = 0; ks < kUnits / 2; ++ks) {
+            if (kSt == 1 && 2 * ks * In::kPer >= d) break;   // (the rest holds zeros)
             const int c = 2 * ks + lhalf;
             unit_t a[TM];
 #pragma unroll
@@ -250,13 +262,10 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
                     for (int x = 0; x < TM; ++x) acc[x][j] = In::mma32(a[x], b[j], acc[x][j], i);
         }
     }
-    // 32x32 accumulator layout: lane holds column lane % 32; register i holds
-    // row 8 (i / 4) + 4 (lane / 32) + i % 4.
-    const auto step = [](int i) { return 8 * (i >> 2) + (i & 3); };
 #pragma unroll
     for (int x = 0; x < TM; ++x) {
         const int t0 = m0 + 32 * (wm * TM + x) + 4 * lhalf;
-        const uint32_t ok = rows_in_range<16>(rows, h_rows, t0, T, step);
+        const uint32_t ok = TM == 1 ? early : checks(x);
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int e = n0 + 32 * (wn * TN + j) + lrow;
@@ -412,7 +421,13 @@ hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_
     }
     const int64_t nm8 = ((T + BM - 1) / BM + 7) / 8 * 8;   // token tiles, whole eights
     const int64_t nn = (E + BN - 1) / BN;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(nm8 * nn)), dim3(kThreads), kLds, stream, H, rows,
+    // Rows of fewer chunks than the ring has stages fill only the first ones:
+    // the LDS left lets more blocks share a compute unit (100000 x 128 x 64 in
+    // bf16: 15.2 us with the whole ring, 12.3).
+    constexpr int kPK = kUnits * In::kPer;
+    const int64_t nk = (d + kPK - 1) / kPK;
+    const size_t bytes = kLds / kSt * (size_t)(nk < kSt ? nk : kSt);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nm8 * nn)), dim3(kThreads), bytes, stream, H, rows,
                        h_rows, W, S, (int)T, (int)E, (int)d);
     return hipGetLastError();
 }
@@ -434,7 +449,9 @@ hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_
 // Blocks of the small kernel share a compute unit, so turns after the first
 // cost it a fifth less (bf16; 8192 x 128 x 2048 in 32 x 32: 31 us). Rows that
 // are not whole 128-byte lines make the pipelined chunks span two (40379 x 26 x
-// 232 in bf16: 256 x 64 tiles 9.9 us, 32 x 32 7.1).
+// 232 in bf16: 256 x 64 tiles 9.9 us, 32 x 32 7.1), which costs the ones of one
+// or two chunks less than the small kernel's turns (100003 x 33 x 40 in fp32: 32
+// x 64 tiles 17.0 us, 256 x 64 16.0).
 // fp32 is bound by the matrix cores at the larger tiles (32 elements a chunk;
 // 65536 x 256 x 2048: 531 us, 130 TFLOP/s; 8192 x 64 x 1024: 17.6 us against 64
 // on the vector units). Its 256 x 256 and 128 x 128 tiles are never the
@@ -448,28 +465,44 @@ constexpr TileCost kTiles[] = {{256, 256, 2.4, 1e30}, {256, 128, 1.55, 4.1}, {25
                                {kST, 64, 0.42, 0.44}, {kST, 32, 0.30, 0.32}};
 constexpr int64_t kComputeUnits = 256;
 
+constexpr int kOneChunk = 8;   // 64 x 64 tiles of a single chunk
+
 template <class In>
 int pick_tile(int64_t T, int64_t E, int64_t d) {
     constexpr bool kBf16 = In::kPer == 8;
-    const bool whole = d * (int64_t)sizeof(typename In::elem_t) % kChunk == 0;
-    int best = 0;
+    const int64_t bytes = d * (int64_t)sizeof(typename In::elem_t);
+    const int64_t chunks = (bytes + kChunk - 1) / kChunk;
+    const bool whole = bytes % kChunk == 0;
+    // A launch of 2^32 threads and more is refused by the runtime.
+    const auto fits = [&](int64_t bm, int64_t bn) {
+        const int64_t blocks = ((T + bm - 1) / bm + 7) / 8 * 8 * ((E + bn - 1) / bn);
+        return blocks * (bm >= 128 ? 512 : 256) < (int64_t)1 << 32;
+    };
+    // One chunk: no ring to fill, and each block is a chain of a few latencies.
+    // The smallest tile puts most blocks on a compute unit (eight) and skips
+    // the part of the chunk past d. 300000 x 8 x 16: bf16 18.9 us in 256 x 64 tiles,
+    // 9.9 in these; fp32 23.6 in 32 x 32, 13.4; through an index 29.2 and 16.7,
+    // 31.7 and 19.3.
+    if (chunks == 1 && E <= 64 && fits(64, 64)) return kOneChunk;
+    int best = -1;
     double low = 0.0;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const TileCost &t = kTiles[i];
+        if (!fits(t.bm, t.bn)) continue;
         const int64_t tiles = ((T + t.bm - 1) / t.bm) * ((E + t.bn - 1) / t.bn);
         const double turns = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
         double cost = turns * (kBf16 ? t.bf16 : t.f32);
         if (t.bm > kST) {
-            if (!whole) cost *= 1.4;
+            if (!whole && chunks > 2) cost *= 1.4;
         } else if (kBf16) {
             cost *= 0.8 + 0.2 / turns;
         }
-        if (i == 0 || cost < low) {
+        if (best < 0 || cost < low) {
             best = i;
             low = cost;
         }
     }
-    return best;
+    return best;   // (-1: none)
 }
 
 template <class In, int NJ>
@@ -489,6 +522,7 @@ hipError_t launch_affinity(const typename In::elem_t *H, const int32_t *rows, in
                            hipStream_t stream) {
     constexpr bool kBf16 = In::kPer == 8;
     switch (pick_tile<In>(T, E, d)) {
+        case -1: return hipErrorInvalidConfiguration;
         case 0:
             if constexpr (kBf16)
                 return launch_pipe<In, 256, 256, 2, 4, 2>(H, rows, h_rows, W, S, T, E, d, stream);
@@ -501,6 +535,8 @@ hipError_t launch_affinity(const typename In::elem_t *H, const int32_t *rows, in
             break;
         case 4: return launch_pipe<In, 128, 64, 1, 1, 4>(H, rows, h_rows, W, S, T, E, d, stream);
         case 5: return launch_pipe<In, 64, 64, 1, 1, 4>(H, rows, h_rows, W, S, T, E, d, stream);
+        case kOneChunk:
+            return launch_pipe<In, 64, 64, 1, 1, 1>(H, rows, h_rows, W, S, T, E, d, stream);
         case 6: return launch_small<In, 4>(H, rows, h_rows, W, S, T, E, d, stream);
         default: break;
     }

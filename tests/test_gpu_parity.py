@@ -122,7 +122,10 @@ def test_affinity_workloads(name):
     ("bf16", 16385, 100, 264), ("bf16", 16385, 60, 56), ("bf16", 8193, 60, 520),
     ("bf16", 7169, 60, 264), ("bf16", 1025, 60, 1000), ("f32", 65025, 120, 40), ("f32", 65025, 50, 32),
     ("f32", 16385, 60, 64), ("f32", 8193, 60, 32), ("f32", 4161, 120, 72), ("f32", 4033, 120, 40),
-    ("f32", 1025, 60, 1000)])
+    ("f32", 1025, 60, 1000),
+    # (a single chunk and up to 64 experts have a tile of their own)
+    ("bf16", 16385, 60, 136), ("f32", 65025, 50, 64), ("f32", 8193, 60, 64),
+    ("bf16", 4097, 64, 8), ("bf16", 63, 1, 24), ("f32", 4097, 17, 24), ("f32", 65, 64, 8)])
 def test_affinity_every_tile(dtype, T, E, d):
     rng = np.random.Generator(np.random.PCG64(T + 7 * E + d))
     H = rng.standard_normal((T, d), dtype=np.float32)
@@ -140,6 +143,25 @@ def test_affinity_every_tile(dtype, T, E, d):
     assert not Sg[~ok].any()
     Hg = Hs[np.where(ok, rows, 0)]
     np.testing.assert_array_equal(Sg[ok], gpu_affinity(Hg, Ws)[ok])
+
+
+def test_affinity_more_tiles_than_a_launch_takes():
+    """2^29 rows: the tile the costs alone would choose makes 2^32 threads, which
+    a launch does not take."""
+    T, E, d = 1 << 29, 2, 72
+    if torch.cuda.mem_get_info()[0] < (T * (d + E) * 4) * 1.05:
+        pytest.skip("needs 160 GB of device memory")
+    H = torch.zeros((T, d), device="cuda")
+    rows = torch.tensor([0, 1, T // 2, T - 257, T - 2, T - 1], device="cuda")
+    rng = np.random.Generator(np.random.PCG64(29))
+    Hs = rng.integers(-8, 9, (len(rows), d)).astype(np.float32)
+    Ws = rng.integers(-8, 9, (E, d)).astype(np.float32)
+    H[rows] = dev(Hs)
+    S = pb.affinity(H, dev(Ws))
+    np.testing.assert_array_equal(host(S[rows]).astype(np.float64), oracle.affinity(Hs, Ws))
+    assert not S[2:T // 2].any()
+    del H, S
+    torch.cuda.empty_cache()
 
 
 # ---------------------------------------------------------------- assign ---
