@@ -76,7 +76,11 @@ const char *base_status_string(int status);
  *
  * Arithmetic: BASE_BF16 multiplies bf16 values on the matrix cores and
  * accumulates in fp32; BASE_F32 multiplies and accumulates in fp32 (no
- * reduced-precision products). The summation order over k is unspecified.
+ * reduced-precision products). The summation order over k is unspecified. It
+ * depends on the sizes and on where a row stands: equal rows of H at different
+ * positions may score differently in the last bits (each within the fp32
+ * accumulation error of the exact product). One call on the same inputs gives
+ * the same bits every time.
  * Errors: BASE_ERR_INVALID_ARG (null/misaligned pointer, size <= 0,
  * d % 8 != 0), BASE_ERR_UNSUPPORTED_DTYPE, BASE_ERR_RANGE, BASE_ERR_HIP.
  */
@@ -97,7 +101,9 @@ int base_affinity(const void *H, const void *W, float *S, int64_t T, int64_t E, 
  *           that range gives a zero row of S; never read out of bounds)
  *   S       [device] N x E float32, row-major, written entirely
  *   N, h_rows <= 2^31 - 1; other arguments and arithmetic as base_affinity
- *   (bit-identical to base_affinity of the gathered rows).
+ *   (bit-identical to base_affinity of the gathered rows, H[rows]; not to the
+ *   rows of base_affinity of H taken afterwards, whose sums may be ordered
+ *   differently).
  * Errors: as base_affinity; rows == NULL is BASE_ERR_INVALID_ARG.
  */
 int base_affinity_gather(const void *H, int64_t h_rows, const int32_t *rows, const void *W,

@@ -186,7 +186,9 @@ def _need_device(*ts) -> None:
 def affinity(H, W, out=None, rows=None, stream=None):
     """S = H . W^T as float32 [T, E] (base_affinity). With `rows` (int32 [N]),
     S[i] = H[rows[i]] . W^T, N rows (base_affinity_gather: the shuffle of
-    tokens to workers read through the index)."""
+    tokens to workers read through the index). The order of a score's sum
+    depends on the row's position, so affinity(H, W, rows=r) equals
+    affinity(H[r], W) bit for bit and affinity(H, W)[r] up to fp32 rounding."""
     torch = _torch()
     _need_device(H, W)
     T, d = H.shape

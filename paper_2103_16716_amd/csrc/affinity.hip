@@ -134,7 +134,13 @@ __device__ inline void bare_barrier() {
 // row strides that are powers of two those fall on few memory channels. H is
 // read once, so its loads are marked non-temporal and leave the L2 to W.
 // T = 32768, E = 128, d = 2048: 39.8 us before, 36.2 with the rotation,
-// 31.5 with both (4.8 TB/s).
+// 31.5 with both (4.8 TB/s); T = 65536, d = 4096, E = 32: 83 us, 118 without the
+// rotation. (When H has just been written and is still in the last-level cache,
+// the loads so marked are slower, 38 us against 33 at the first size; when it has
+// not, 35 against 53.) The rotation gives a row's sum an order that depends on
+// its tile. Sums of two or four parts, each always in the same order and added in
+// the same order, would not: they need the parts' registers, and at the same
+// sizes took 41-44 and 90-120 us.
 constexpr int kChunk = 128;          // bytes of a row per stage
 constexpr int kUnits = kChunk / 16;
 constexpr int kNonTemporal = 2;      // cache policy bit of the LDS-direct load

@@ -145,6 +145,29 @@ def test_affinity_every_tile(dtype, T, E, d):
     np.testing.assert_array_equal(Sg[ok], gpu_affinity(Hg, Ws)[ok])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_affinity_equal_rows_at_different_positions(dtype):
+    """A row's sum is ordered by its position: equal rows agree within the
+    rounding of two fp32 sums, in any tile and through an index."""
+    T, E, d, n = 33000, 100, 1024, 40
+    rng = np.random.Generator(np.random.PCG64(5))
+    H = rng.standard_normal((n, d), dtype=np.float32)
+    W = rng.standard_normal((E, d), dtype=np.float32) / np.float32(np.sqrt(d))
+    Hs, Ws = H, W
+    if dtype == "bf16":
+        Hs, Ws = wl.f32_to_bf16_bits(H), wl.f32_to_bf16_bits(W)
+        H, W = wl.bf16_bits_to_f32(Hs), wl.bf16_bits_to_f32(Ws)
+    bound = 2.0 * fp32_accumulation_bound(H, W)
+    which = rng.integers(0, n, T)
+    S = gpu_affinity(Hs[which], Ws)
+    rows = rng.permutation(T).astype(np.int32)
+    Sg = host(pb.affinity(dev(Hs[which]), dev(Ws), rows=dev(rows)))
+    first = np.stack([S[np.flatnonzero(which == k)[0]] for k in range(n)])
+    assert np.all(np.abs(S - first[which]) <= bound[which])
+    assert np.all(np.abs(Sg - first[which[rows]]) <= bound[which[rows]])
+    np.testing.assert_array_equal(S, gpu_affinity(Hs[which], Ws))   # the same bits again
+
+
 def test_affinity_more_tiles_than_a_launch_takes():
     """2^29 rows: the tile the costs alone would choose makes 2^32 threads, which
     a launch does not take."""
