@@ -638,8 +638,9 @@ __device__ __attribute__((always_inline)) inline uint32_t group_max_u32(uint32_t
 // images in o, valid: t < T). Bound by instructions, so the selection runs on
 // 32-bit keys: the image with its low bits replaced by the expert (the lower
 // expert higher), one max or min per comparison. Each lane sorts its eight
-// keys (a network of 19 comparators); nine rounds take the highest head of
-// the group and the lane that owned it moves on. The lanes then read the
+// keys (a sorting network of 19 comparators, the fewest for eight); nine
+// rounds take the highest head of the group and the lane that owned it moves
+// on. The lanes then read the
 // chosen scores back by their experts. The bound is the 9th key with its low
 // bits set, at or above every score left out. (Nine rounds of a maximum over
 // all scores with their experts took about twice the time: 256 problems of T =
@@ -1922,16 +1923,17 @@ __global__ __launch_bounds__(kThreads) void update_wide_kernel(Ctx<M> c0) {
 //
 // The rounds of a phase that have more active tokens than the engine takes:
 // a few blocks per problem (128 for a single one, half the compute units) run
-// them back to back in one launch, two grid barriers a round. Bound by latency, so the round
-// is laid out for few dependent trips to memory and no atomic on it:
+// them back to back in one launch, two grid barriers a round. Bound by latency,
+// so the round is laid out for few dependent trips to memory and no atomic on
+// it:
 //   - Block b owns positions [b per, (b + 1) per) of the phase's bid table
 //     and the experts [b pe, (b + 1) pe). Its active tokens sit at the front
 //     of its positions, so their number is the only count others need.
 //   - A bid goes to its token's own position (key, expert): nothing is
 //     reserved, nothing collides on a popular expert.
 //   - After a barrier the owner of an expert scans the experts of all bids
-//     (two bytes each, only the filled front of every block's positions) and
-//     collects its own. It keeps the C largest keys of holders and bids; the
+//     (a byte each, two with more than 256 experts, and only the filled front
+//     of every block's positions) and collects its own. It keeps the C largest keys of holders and bids; the
 //     token each bid leaves active (the bidder refused, the holder it
 //     displaced, none for a free slot) goes to the bid's position of an out
 //     table.
@@ -1943,8 +1945,9 @@ __global__ __launch_bounds__(kThreads) void update_wide_kernel(Ctx<M> c0) {
 // one has arrived. Everything that crosses blocks goes by agent-scope stores
 // and loads, so no barrier writes back or invalidates a cache.
 //
-// A round of a few hundred active tokens takes about 10 us: ten dependent trips to memory (prices,
-// summaries, bids, flags, ...) of some 0.8 us, and the selections. With a
+// A round of a few hundred active tokens takes about 10 us: ten dependent trips
+// to memory (prices, summaries, bids, flags, ...) of some 0.8 us, and the
+// selections. With a
 // counter barrier, device-scope fences and bucket slots reserved by atomics
 // (about 70 ns each on one address) it took 26. Solves: T = 65536, E = 256
 // 3480 -> 2955 us, T = 32768, E = 128 (clustered) 991 -> 903, T = 2048, E = 128
@@ -3009,7 +3012,6 @@ __global__ __launch_bounds__(kLoopThreads, 4) void round_loop_kernel(Ctx<M> c0, 
         n = s_sum;
         const int m_old = m;
         for (int j0 = 0; j0 < m_old; j0 += kLoopThreads) {
-            // (a pass reads its positions before any of it is packed over them)
             const int j = j0 + tid;
             int t = j < m_old ? ld_agent(&out[base + j]) : -1;
             if (t >= c.T) {
@@ -5487,7 +5489,9 @@ template <class M, int G>
 __global__ __launch_bounds__(kSmallThreads) void small_solve_kernel(Ctx<M> c0, AssignParams p,
                                                                     int ssp_cap, int nslots,
                                                                     int fallbacks) {
-    constexpr int Ep = 8 * G > 256 ? 256 : (8 * G < 32 ? 32 : 8 * G);   // E <= kSmallE = 256
+    constexpr int Ep = 8 * G < 32 ? 32 : 8 * G;
+    static_assert(Ep <= kSmallE, "instances the driver takes");
+    static_assert(kSmallThreads == ssp_block<Ep>(), "the finish runs in this kernel's block");
     const Ctx<M> c = c0.at(blockIdx.y);
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if constexpr (M::kInteger) {   // no shortest-path finish: one call to the end
@@ -6379,18 +6383,20 @@ hipError_t run_solve(const Ctx<M> &c0, const AssignParams &p, int B, int32_t *as
     hipLaunchKernelGGL((prologue_kernel<M, G>), dim3(sblocks, B), dim3(kThreads), 0, s, c, p,
                        assign, rpart);
     hipLaunchKernelGGL(start_kernel<M>, dim3(1, B), dim3(256), 0, s, c, p, rpart, sblocks);
-    // Small problems: every phase's rounds in one workgroup per problem
-    // (small_solve_kernel), the shortest-path finish after each; the last
-    // slot's launch runs every phase left to the end.
-    // By default a batch of at least kSmallBatch problems (each would get a
-    // fraction of the device in the multi-kernel path; 256 worker-shape
-    // problems take 3.9 ms this way against 12.3 ms) and very small
-    // problems; a single worker-shape problem is faster with the whole
-    // device (0.88 ms against 1.20 ms).
+    // Small problems: the whole solve in one launch of one workgroup per
+    // problem (small_solve_kernel). By default a batch of at least kSmallBatch
+    // problems, each of which would get a fraction of the device in the
+    // multi-kernel path (T = 2048, E = 128: 256 problems 1.75 ms this way, 9.98
+    // that way, 8 problems 1.14 and 1.24), and very small single problems (T =
+    // 512: E = 8 138 us and 319, E = 64 359 and 457). A larger single problem
+    // is faster with the whole device from about T E = 2^17 on (T = 2048: E = 256
+    // 2408 us and 1456, E = 128 988 and 770, E = 64 593 and 559; E = 16 289 and
+    // 388); the line stays at T alone because the two ways' results differ.
     const int small_set = small_path_setting();
     const bool small_fits = c.T <= kSmallT && c.E <= kSmallE;
     const bool small = small_fits && (small_set == 1 ||
                                       (small_set < 0 && (B >= kSmallBatch || c.T <= kSmallSoloT)));
+    if constexpr (8 * G <= kSmallE)   // (the widest row such a problem has)
     if (small) {
         const size_t bytes =
             std::max(small_lds(c.T, c.E, (int)sizeof(value_t)).total, ssp_r > 0 ? ssp_bytes : 0);
