@@ -50,7 +50,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 matrix-core peak, TFLOP/s
 UNPERMUTE_WORKLOADS = {"t65536-e256-d4096"}
 COLD_STEPS = 5                 # steps timed after evicting the caches
-ENGINE_KERNEL = "engine_kernel"   # the solve's dominant kernel (rounds with few active tokens)
+ENGINE_KERNEL = "engine_kernel"   # the rounds with few active tokens, in one workgroup
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -503,7 +503,7 @@ def main():
 
     events = [[torch.cuda.Event(enable_timing=True) for _ in range(n_ev)] for _ in range(args.steps)]
     # The library brackets each engine launch with its own events on the same
-    # stream (base_timing_enable), so the dominant kernel is timed live.
+    # stream (base_timing_enable), so that kernel is timed live.
     pb.timing_enable(64 * args.steps)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -570,7 +570,8 @@ def main():
     if unpermute:
         rl["unpermute"] = ("hbm", bytes_perm / (per_call_ms["unpermute"] * 1e-3) / 1e9,
                            HBM_PEAK_GBS, "GB/s", bytes_perm)
-    # The dominant kernel: the engine (the largest part of the assign call).
+    # The timed kernel: the engine (about a third of the assign call; the round
+    # loop takes more of it at the headline shape, see share_of_step).
     # Its modelled bytes per launch are the bids it places times the bytes a
     # bid would need if it read the token's whole score row (4E bytes) plus
     # a 16-byte key and expert, over the launches of one solve. This is an

@@ -233,9 +233,15 @@ int base_assign(const void *S, int s_dtype, int64_t T, int64_t E, const base_ass
  * Sec. 3.2.1 (Sharding): the assignment over all workers is split into
  * independent problems, one per worker, each of T tokens and E experts (the
  * paper's runs: T = 2 x 1024, E = 128, Sec. 4.1). This call solves B such
- * problems together on one device, every problem exactly as base_assign
- * would (same algorithm, same options, bit-identical results); the
- * single-workgroup parts of the solve run for all problems at once.
+ * problems together on one device, every problem as base_assign would: same
+ * algorithm, options and bound. The single-workgroup parts of the solve run
+ * for all problems at once. Results are bit-identical to base_assign's where
+ * both solve a problem the same way and, in float mode, no two moves of the
+ * shortest-path finish cost exactly the same (it may then take either one).
+ * Batches of eight and more with T <= 2048 and E <= 256 solve each problem in
+ * one workgroup, as base_assign does up to T = 512; that way ends the phases
+ * above the last at other rounds, so that its results may be another
+ * assignment within the bound.
  * Sec. 3.2.1 (Shuffling) routes tokens to workers at random before the
  * solve: base_affinity_gather computes the scores of the shuffled rows, and
  * base_permute_batched / base_gate_combine_batched route them, all reading
@@ -443,9 +449,9 @@ int base_gate_backward(const void *dY, const void *F, const void *H, const void 
 /* ------------------------------------------------------------------------ */
 /*
  * Not part of the path. While enabled, base_assign brackets every launch of
- * its single-workgroup engine kernel (the rounds of a phase with few active
- * tokens: most of a solve's time) with a pair of HIP events recorded on the
- * call's stream, so a tool can time that kernel over a stretch of ordinary
+ * its single-workgroup kernel (the engine: the rounds of a phase with few
+ * active tokens; for problems small enough, the kernel that solves them
+ * whole) with a pair of HIP events recorded on the call's stream, so a tool can time that kernel over a stretch of ordinary
  * calls. At most `capacity` launches are recorded; later ones are not.
  *
  * base_timing_enable(capacity) creates 2 * capacity events on the current

@@ -271,9 +271,9 @@ def test_assign_without_the_engine_integer_and_fallback():
 
 
 def test_assign_batched_more_problems_than_compute_units():
-    """300 problems: more than the 256 compute units, so the batch runs
-    without the round loop (its blocks could not all be resident); each
-    problem still equals its own solve."""
+    """300 problems of 256 tokens: more workgroups than the 256 compute units
+    in the one-launch solve; each problem still equals its own, which runs the
+    same way. (Larger problems in such numbers: test_gpu_round_loop.py.)"""
     B, T, E = 300, 256, 8
     rng = np.random.Generator(np.random.PCG64(301))
     S = rng.standard_normal((B, T, E), dtype=np.float32)
@@ -455,8 +455,10 @@ def _worker_batch(B, seed0):
 def test_assign_batched_identical_to_single_solves(monkeypatch, route):
     """Sec. 3.2.1 (Sharding): B independent worker problems in one call give,
     problem by problem, exactly what base_assign gives for each alone, and
-    each meets the oracle's bound; on the default route and with the
-    single-workgroup rounds forced on and off."""
+    each meets the oracle's bound; on the default route (below eight problems
+    the same as a single solve's) and with the single-workgroup rounds forced on
+    and off. From eight problems on the default routes differ: the bound is what
+    the next test checks there."""
     if route is not None:
         monkeypatch.setenv("BASE_SMALL_PATH", route)
     B = 6
@@ -474,6 +476,21 @@ def test_assign_batched_identical_to_single_solves(monkeypatch, route):
     assert res.stats.bids == bids
     batch_eps = max(eps_expected(host(S[b]), EPS_FINAL) for b in range(B))
     for b in (0, B - 1):
+        S64 = host(S[b]).astype(np.float64)
+        a_opt, obj_opt, _ = oracle.solve_ssp(S64)
+        one = pb.AssignResult(res.assign[b], res.perm[b], res.prices[b], res.stats)
+        check_assignment(S64, one, EPS_FINAL, opt=(a_opt, obj_opt), batch_eps=batch_eps)
+
+
+def test_assign_batched_from_eight_problems_on_meets_the_bound():
+    """Batches of eight and more solve each problem in one workgroup, single
+    problems of this size do not: the assignments may differ, each within the
+    bound of the optimum."""
+    S = _worker_batch(8, 950)
+    res = pb.assign_batched(S)
+    T, E = S.shape[1], S.shape[2]
+    batch_eps = max(eps_expected(host(S[b]), EPS_FINAL) for b in range(8))
+    for b in (0, 3, 7):
         S64 = host(S[b]).astype(np.float64)
         a_opt, obj_opt, _ = oracle.solve_ssp(S64)
         one = pb.AssignResult(res.assign[b], res.perm[b], res.prices[b], res.stats)
