@@ -451,8 +451,9 @@ int base_gate_backward(const void *dY, const void *F, const void *H, const void 
  * Not part of the path. While enabled, base_assign brackets every launch of
  * its single-workgroup kernel (the engine: the rounds of a phase with few
  * active tokens; for problems small enough, the kernel that solves them
- * whole) with a pair of HIP events recorded on the call's stream, so a tool can time that kernel over a stretch of ordinary
- * calls. At most `capacity` launches are recorded; later ones are not.
+ * whole) with a pair of HIP events recorded on the call's stream, so a tool
+ * can time that kernel over a stretch of ordinary calls. At most `capacity`
+ * launches are recorded; later ones are not.
  *
  * base_timing_enable(capacity) creates 2 * capacity events on the current
  * device and clears the record; capacity <= 0 destroys them and disables the

@@ -106,11 +106,12 @@ __device__ inline void tile_of(int L, int nn, int &mt, int &nt) {
 // --------------------------------------------------------- pipelined GEMM --
 
 // Waits until at most N vector-memory operations of this wave are in flight
-// (the LDS-direct loads count until their data is in LDS).
+// (the LDS-direct loads count until their data is in LDS) and its LDS reads
+// are done: the stage they read is refilled after the barrier that follows.
 template <int N>
 __device__ inline void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt field");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
 // Workgroup barrier with no memory wait of its own: each wave has already
