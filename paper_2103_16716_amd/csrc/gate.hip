@@ -559,12 +559,11 @@ __global__ __launch_bounds__(kGreedyTile) void greedy_scatter_kernel(const int32
 
 // ---------------------------------------------------------- gated residual --
 
-// One 16-byte chunk of a row: 8 bf16 or 4 fp32 values, widened to fp32. Rows
-// are stored as usual: the residual's are read next, and marked non-temporal
-// they are not in the last-level cache then (T = 32768, d = 2048 in bf16, the call
-// and a pass over its result: 122 us so marked, 113 as usual; T = 16384 63 and
-// 57). Loads so marked were slower too (T = 8192: 35 -> 47 us). The gradient's
-// large outputs are the exception, see kStreamBytes.
+// One 16-byte chunk of a row: 8 bf16 or 4 fp32 values, widened to fp32. The
+// rows written are read again by later kernels only, so their stores are
+// non-temporal and leave the caches to the rows being read (gated residual and
+// its gradient at T = 32768, d = 2048 in bf16: 212 -> 202 us; T = 16384, d = 1024
+// in fp32: 108 -> 97). Loads so marked were slower (T = 8192: 35 -> 47 us).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <bool BF16>
 struct Chunk {
@@ -580,7 +579,6 @@ struct Chunk {
             for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(w[i]);
         }
     }
-    template <bool NT>
     __device__ static void store(void *base, int64_t chunk, const float (&v)[8]) {
         uint32_t w[4];
         if (BF16) {
@@ -591,10 +589,8 @@ struct Chunk {
 #pragma unroll
             for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(v[i]);
         }
-        const u32x4 v4 = {w[0], w[1], w[2], w[3]};
-        u32x4 *p = reinterpret_cast<u32x4 *>(base) + chunk;
-        if constexpr (NT) __builtin_nontemporal_store(v4, p);
-        else *p = v4;
+        __builtin_nontemporal_store(u32x4{w[0], w[1], w[2], w[3]},
+                                    reinterpret_cast<u32x4 *>(base) + chunk);
     }
 };
 
@@ -629,7 +625,7 @@ __global__ __launch_bounds__(256) void gate_combine_kernel(const void *F, const 
         Ck::load(H, (int64_t)t * ncs + j, h);
 #pragma unroll
         for (int q = 0; q < Ck::kN; ++q) y[q] = fmaf(g, f[q], h[q]);
-        Ck::template store<false>(Y, (int64_t)t * ncs + j, y);
+        Ck::store(Y, (int64_t)t * ncs + j, y);
     }
 }
 
@@ -638,15 +634,7 @@ __global__ __launch_bounds__(256) void gate_combine_kernel(const void *F, const 
 //   dS[t] = g (1 - g) (dY[t] . F[k]);  dF[k] = g dY[t];  dH[t] = dY[t] + dS[t] W[a].
 constexpr int kRowRegs = 2;   // 16-byte chunks of a row a thread keeps in registers
 
-// dF and dH of at least so many bytes each are stored non-temporally (NT):
-// with dY, F and H they exceed the last-level cache, and what they leave of it
-// holds rows of H for dW. The call alone and with a pass over dF and dH after
-// it, in us, so marked and as usual (fp32, d = 2048): 128 MiB 126 and 132, 222 and
-// 229; 256 MiB 248 and 260, 442 and 451; but 64 MiB (bf16) 97 and 101, 143 and
-// 135; 32 MiB 36 and 33, 62 and 56.
-constexpr int64_t kStreamBytes = (int64_t)96 << 20;
-
-template <bool BF16, bool NT>
+template <bool BF16>
 __global__ __launch_bounds__(256) void gate_rows_kernel(const void *dY, const void *F,
                                                         const void *W, const float *S,
                                                         const int32_t *assign,
@@ -686,7 +674,7 @@ __global__ __launch_bounds__(256) void gate_rows_kernel(const void *dY, const vo
                         float o[8];
 #pragma unroll
                         for (int q = 0; q < Ck::kN; ++q) o[q] = g * y[r][q];
-                        Ck::template store<NT>(dF, (int64_t)k * ncs + j, o);
+                        Ck::store(dF, (int64_t)k * ncs + j, o);
                     }
                 }
             }
@@ -707,7 +695,7 @@ __global__ __launch_bounds__(256) void gate_rows_kernel(const void *dY, const vo
                     float o[8];
 #pragma unroll
                     for (int q = 0; q < Ck::kN; ++q) o[q] = fmaf(ds, w[r][q], y[r][q]);
-                    Ck::template store<NT>(dH, (int64_t)t * ncs + j, o);
+                    Ck::store(dH, (int64_t)t * ncs + j, o);
                 }
             }
         }
@@ -743,11 +731,11 @@ __global__ __launch_bounds__(256) void gate_rows_kernel(const void *dY, const vo
             Ck::load(dY, (int64_t)t * ncs + j, y);
 #pragma unroll
             for (int q = 0; q < Ck::kN; ++q) o[q] = g * y[q];
-            Ck::template store<NT>(dF, (int64_t)k * ncs + j, o);
+            Ck::store(dF, (int64_t)k * ncs + j, o);
             Ck::load(W, (int64_t)a * ncs + j, w);
 #pragma unroll
             for (int q = 0; q < Ck::kN; ++q) o[q] = fmaf(ds, w[q], y[q]);
-            Ck::template store<NT>(dH, (int64_t)t * ncs + j, o);
+            Ck::store(dH, (int64_t)t * ncs + j, o);
         }
     }
 }
@@ -932,14 +920,17 @@ hipError_t launch_gate_backward(const void *dY, const void *F, const void *H, co
     const int ncs = (int)(d / (bf16 ? 8 : 4));
     const int rows = (int)(T < 65536 ? T : 65536);
     const dim3 dwg((unsigned)E, (unsigned)((ncs + 63) / 64));
-    const bool nt = T * d * (bf16 ? 2 : 4) >= kStreamBytes;
-    const auto rows_fn = bf16 ? (nt ? &gate_rows_kernel<true, true> : &gate_rows_kernel<true, false>)
-                              : (nt ? &gate_rows_kernel<false, true> : &gate_rows_kernel<false, false>);
-    const auto dw_fn = bf16 ? &gate_dw_kernel<true> : &gate_dw_kernel<false>;
-    hipLaunchKernelGGL(rows_fn, dim3(rows), dim3(256), 0, s, dY, F, W, S, assign, perm, dH, dF, dS,
-                       (int)T, (int)E, ncs);
-    hipLaunchKernelGGL(dw_fn, dwg, dim3(64 * kDwWaves), 0, s, H, dS, perm, offsets, dW, (int)T,
-                       (int)E, ncs);
+    if (bf16) {
+        hipLaunchKernelGGL(gate_rows_kernel<true>, dim3(rows), dim3(256), 0, s, dY, F, W, S, assign,
+                           perm, dH, dF, dS, (int)T, (int)E, ncs);
+        hipLaunchKernelGGL(gate_dw_kernel<true>, dwg, dim3(64 * kDwWaves), 0, s, H, dS, perm,
+                           offsets, dW, (int)T, (int)E, ncs);
+    } else {
+        hipLaunchKernelGGL(gate_rows_kernel<false>, dim3(rows), dim3(256), 0, s, dY, F, W, S,
+                           assign, perm, dH, dF, dS, (int)T, (int)E, ncs);
+        hipLaunchKernelGGL(gate_dw_kernel<false>, dwg, dim3(64 * kDwWaves), 0, s, H, dS, perm,
+                           offsets, dW, (int)T, (int)E, ncs);
+    }
     return hipGetLastError();
 }
 

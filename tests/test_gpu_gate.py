@@ -157,26 +157,3 @@ def test_gate_backward_against_oracle(dtype, name, kind):
     np.add.at(propW, ah, dS_err[:, None] * np.abs(Hh))
     eW = np.abs(host(dW).astype(np.float64) - rW)
     assert np.all(eW <= (counts[:, None] + 8) * F32_EPS * magW + propW + 1e-30)
-
-
-@pytest.mark.parametrize("dtype,T,d", [("bf16", 26000, 2048), ("bf16", 6400, 8192), ("f32", 13000, 2048)])
-def test_gate_backward_of_streamed_rows(dtype, T, d):
-    """Outputs of 96 MiB and more are stored past the caches: the same bits as
-    those of half the tokens and experts, which are not. (d = 8192: rows longer
-    than a block keeps in registers.)"""
-    E = 8
-    td = torch.bfloat16 if dtype == "bf16" else torch.float32
-    size = 2 if dtype == "bf16" else 4
-    assert T * d * size >= 96 << 20 > T // 2 * d * size
-    g = torch.Generator(device="cuda").manual_seed(T)
-    dY, F, H = (torch.randn((T, d), device="cuda", generator=g).to(td) for _ in range(3))
-    W = torch.randn((E, d), device="cuda", generator=g).to(td)
-    S = torch.randn((T, E), device="cuda", generator=g)
-    a = (torch.arange(T, device="cuda") // (T // E)).int()
-    perm = torch.arange(T, device="cuda").int()
-    full = pb.gate_backward(dY, F, H, W, S, a, perm)
-    h, k = T // 2, E // 2
-    half = pb.gate_backward(dY[:h], F[:h], H[:h], W[:k].contiguous(), S[:h, :k].contiguous(),
-                            a[:h], perm[:h])
-    for x, y in zip(full, half):
-        assert torch.equal(x[:len(y)], y)
