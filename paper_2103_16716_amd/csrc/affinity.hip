@@ -133,12 +133,11 @@ __device__ inline void bare_barrier() {
 // Token tile mt starts at chunk mt % nk and goes round. Without that, all
 // blocks read the same 128 bytes of every row at about the same time, and with
 // row strides that are powers of two those fall on few memory channels. H is
-// read once, so its loads are marked non-temporal and leave the L2 to W.
+// read once, so its loads are marked non-temporal where that pays (kNt, see
+// kStreamFrom) and leave the L2 to W.
 // T = 32768, E = 128, d = 2048: 39.8 us before, 36.2 with the rotation,
 // 31.5 with both (4.8 TB/s); T = 65536, d = 4096, E = 32: 83 us, 118 without the
-// rotation. (When H has just been written and is still in the last-level cache,
-// the loads so marked are slower, 38 us against 33 at the first size; when it has
-// not, 35 against 53.) The rotation gives a row's sum an order that depends on
+// rotation. The rotation gives a row's sum an order that depends on
 // its tile. Sums of two or four parts, each always in the same order and added in
 // the same order, would not: they need the parts' registers, and at the same
 // sizes took 41-44 and 90-120 us.
@@ -148,7 +147,7 @@ constexpr int kNonTemporal = 2;      // cache policy bit of the LDS-direct load
 
 __device__ const uint4 zero_unit = {0, 0, 0, 0};
 
-template <class In, int BM, int BN, int TM, int TN, int kSt>
+template <class In, int BM, int BN, int TM, int TN, int kSt, bool kNt>
 __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affinity_pipe_kernel(
     const typename In::elem_t *__restrict__ H, const int32_t *__restrict__ rows, int64_t h_rows,
     const typename In::elem_t *__restrict__ W, float *__restrict__ S, int T, int E, int d) {
@@ -214,7 +213,8 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
         for (int i = 0; i < kSa; ++i)
             __builtin_amdgcn_global_load_lds(
                 in ? (const void *)(ga[i] + k) : (const void *)&zero_unit,
-                (BASE_LDS void *)(base + (i * kThreads + wave * 64) * 16), 16, 0, kNonTemporal);
+                (BASE_LDS void *)(base + (i * kThreads + wave * 64) * 16), 16, 0,
+                kNt ? kNonTemporal : 0);
 #pragma unroll
         for (int i = 0; i < kSb; ++i)
             __builtin_amdgcn_global_load_lds(
@@ -404,13 +404,13 @@ __global__ __launch_bounds__(64 * kSWaves) void affinity_small_kernel(
     }
 }
 
-template <class In, int BM, int BN, int TM, int TN, int kSt>
-hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_t h_rows,
+template <class In, int BM, int BN, int TM, int TN, int kSt, bool kNt>
+hipError_t launch_pipe_as(const typename In::elem_t *H, const int32_t *rows, int64_t h_rows,
                        const typename In::elem_t *W, float *S, int64_t T, int64_t E, int64_t d,
                        hipStream_t stream) {
     constexpr size_t kLds = (size_t)kSt * (BM + BN) * kChunk;
     constexpr int kThreads = 64 * (BM / (32 * TM)) * (BN / (32 * TN));
-    const auto kernel = &affinity_pipe_kernel<In, BM, BN, TM, TN, kSt>;
+    const auto kernel = &affinity_pipe_kernel<In, BM, BN, TM, TN, kSt, kNt>;
     // The LDS ring is above the default 64 KiB: opted in once per device.
     static std::mutex m;
     static bool granted[64] = {};
@@ -437,6 +437,26 @@ hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_
     hipLaunchKernelGGL(kernel, dim3((unsigned)(nm8 * nn)), dim3(kThreads), bytes, stream, H, rows,
                        h_rows, W, S, (int)T, (int)E, (int)d);
     return hipGetLastError();
+}
+
+// H of so many bytes and more is loaded non-temporally; a smaller one stays in
+// the last-level cache for the permute that reads it next. Affinity and then
+// permute in us, H just written / other data written since, so marked and not
+// (bf16, d = 2048; 512 MiB: E = 256, d = 4096): 32 MiB 37 / 37 and 34 / 34; 64 MiB 56 /
+// 53 and 49 / 57; 128 MiB 94 / 83 and 81 / 100; 256 MiB 153 / 145 and 154 / 177; 512
+// MiB 328 / 329 and 317 / 317, of which the affinity 149 and 157.
+constexpr int64_t kStreamFrom = (int64_t)48 << 20;
+
+template <class In, int BM, int BN, int TM, int TN, int kSt>
+hipError_t launch_pipe(const typename In::elem_t *H, const int32_t *rows, int64_t h_rows,
+                       const typename In::elem_t *W, float *S, int64_t T, int64_t E, int64_t d,
+                       hipStream_t stream) {
+    const int64_t bytes = T * d * (int64_t)sizeof(typename In::elem_t);
+    if constexpr (kSt > 1)   // (not tiles of a single chunk)
+        if (bytes >= kStreamFrom)
+            return launch_pipe_as<In, BM, BN, TM, TN, kSt, true>(H, rows, h_rows, W, S, T, E, d,
+                                                                 stream);
+    return launch_pipe_as<In, BM, BN, TM, TN, kSt, false>(H, rows, h_rows, W, S, T, E, d, stream);
 }
 
 // The choice of tile. A product in BM x BN tiles takes about
