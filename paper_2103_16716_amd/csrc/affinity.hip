@@ -76,8 +76,8 @@ __device__ inline int64_t source_row(const int32_t *rows, int64_t h_rows, int i)
 // Whether S rows t0 + step(0), ..., t0 + step(N - 1) have a source row in range:
 // bit i of the result. Rows past T repeat the last one, so that the N loads
 // are issued together; a test at each store made every one wait for its own
-// load or branch (a call in bf16, 6000 x 100 x 1000: 12.1 us, now 10.4; 40379 x
-// 26 x 232 through an index: 9.9, now 9.1).
+// load or branch (a call in bf16, 6000 x 100 x 1000: 12.1 us, then 10.4; 40379 x
+// 26 x 232 through an index: 9.9, then 9.1).
 template <int N, class Step>
 __device__ inline uint32_t rows_in_range(const int32_t *rows, int64_t h_rows, int t0, int T,
                                          Step step) {
@@ -294,9 +294,10 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * (BN / (32 * TN))) void affi
 // instruction covers 16 rows x 64 bytes; two register sets of kSU steps in
 // flight). The waves' partial tiles are added in LDS in wave order (a fixed
 // order: the result does not depend on scheduling), NJ / 2 tiles per wave.
-// Bound by what a compute unit draws from the L2 (about 20 bytes a clock), so
-// 64 experts a block where there are blocks enough: fp32, 8192 x 64 x 1024,
-// 17.6 us against 21.5 at 32 experts.
+// Bound by the loads' latency, with two short register sets in flight (fp32,
+// 8192 x 64 x 1024: a compute unit draws 9 bytes a clock from the L2, 62 TFLOP/s),
+// so 64 experts a block where there are blocks enough, which load a quarter
+// less per output: 17.6 us against 21.5 at 32 experts.
 constexpr int kST = 32;
 constexpr int kSWaves = 4;
 

@@ -563,7 +563,12 @@ __global__ __launch_bounds__(kGreedyTile) void greedy_scatter_kernel(const int32
 // rows written are read again by later kernels only, so their stores are
 // non-temporal and leave the caches to the rows being read (gated residual and
 // its gradient at T = 32768, d = 2048 in bf16: 212 -> 202 us; T = 16384, d = 1024
-// in fp32: 108 -> 97). Loads so marked were slower (T = 8192: 35 -> 47 us).
+// in fp32: 108 -> 97). A pass over the results right after finds less of them in
+// the caches: residual and pass at T = 16384, d = 2048 in bf16 57 us with ordinary
+// stores, 63 so marked. A forward and backward step with the passes that write
+// its inputs and read its results: 64 MiB a matrix 269 and 262 us, 128 MiB 523 and
+// 515, 16 MiB 81 either way, 26 MiB 93 and 96. Loads so marked were slower (T =
+// 8192: 35 -> 47 us).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <bool BF16>
 struct Chunk {
